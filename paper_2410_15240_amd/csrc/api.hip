@@ -567,8 +567,8 @@ FT_EXPORT int fastrack_gcm_decrypt_verify(const uint8_t *key, const uint8_t *bas
 
 namespace {
 constexpr size_t kNoAllocKeyBytes = (sizeof(KeyCtx) + 255) & ~(size_t)255;
-constexpr uint64_t kNoAllocEntries = (FASTRACK_NOALLOC_SCRATCH_BYTES - kNoAllocKeyBytes) / 16;
-static_assert(kNoAllocEntries == FASTRACK_NOALLOC_MAX_PARTIALS, "header constant matches the layout");
+constexpr uint64_t kNoAllocEntries = FASTRACK_NOALLOC_MAX_PARTIALS;
+static_assert(kNoAllocKeyBytes + kNoAllocEntries * 16 <= FASTRACK_NOALLOC_SCRATCH_BYTES, "the header's limit fits the area");
 }  // namespace
 
 static __device__ __align__(256) uint8_t scratch[FASTRACK_NOALLOC_SCRATCH_BYTES];

@@ -237,59 +237,27 @@ __device__ inline u4 mul_tab4(const u4 &x, const Tab4 *__restrict__ t)
     return z;
 }
 
-// The same product with the eight lookups of each word in flight together
-// (the scheduling barrier keeps the batches apart, so at most 32 VGPRs hold
-// table entries): for latency-bound callers that run few multiplies in sequence.
-__device__ inline u4 mul_tab4_b8(const u4 &x, const Tab4 *__restrict__ t)
+// XOR into z the entries of N consecutive nibble positions (8 or 4) of a 4-bit
+// table, t the byte address of the first position's entries. Byte k of w holds
+// positions 2k (high nibble) and 2k + 1 (low nibble), as in mul_tab4. The N
+// lookups are in flight together.
+template <int N>
+__device__ __forceinline__ void tab4_sum(u4 &z, uint32_t w, const char *__restrict__ t)
 {
-    u4 z = {{0u, 0u, 0u, 0u}};
+    uint4 e[N];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t w = x.w[j];
-        uint4 e[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const uint32_t byte = (w >> (8 * (q >> 1))) & 0xFFu;
-            const uint32_t nib = (q & 1) ? (byte & 0xFu) : (byte >> 4);
-            e[q] = *reinterpret_cast<const uint4 *>(t->e[8 * j + q][nib]);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; q += 2) {
-            z.w[0] = xor3(z.w[0], e[q].x, e[q + 1].x);
-            z.w[1] = xor3(z.w[1], e[q].y, e[q + 1].y);
-            z.w[2] = xor3(z.w[2], e[q].z, e[q + 1].z);
-            z.w[3] = xor3(z.w[3], e[q].w, e[q + 1].w);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int k = 0; k < N / 2; ++k) {
+        const uint32_t hi = (w >> (8 * k)) & 0xF0u, lo = (k ? w >> (8 * k - 4) : w << 4) & 0xF0u;
+        e[2 * k] = *reinterpret_cast<const uint4 *>(t + hi + 512 * k);
+        e[2 * k + 1] = *reinterpret_cast<const uint4 *>(t + lo + 512 * k + 256);
     }
-    return z;
-}
-
-// X . Y with Y's 8-bit positional table in global memory, entry (byte position k,
-// value v) at t[v * 16 + k], the 16 lookups in two batches of eight: for the few
-// lanes of the last levels of a lane combine.
-__device__ inline u4 mul_tab8_b8(const u4 &x, const uint4 *__restrict__ t)
-{
-    u4 z = {{0u, 0u, 0u, 0u}};
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        uint4 e[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int k = 8 * h + q;
-            const uint32_t v = (x.w[k >> 2] >> (8 * (k & 3))) & 0xFFu;
-            e[q] = t[v * 16 + k];
-        }
-#pragma unroll
-        for (int q = 0; q < 8; q += 2) {
-            z.w[0] = xor3(z.w[0], e[q].x, e[q + 1].x);
-            z.w[1] = xor3(z.w[1], e[q].y, e[q + 1].y);
-            z.w[2] = xor3(z.w[2], e[q].z, e[q + 1].z);
-            z.w[3] = xor3(z.w[3], e[q].w, e[q + 1].w);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int q = 0; q < N; q += 2) {
+        z.w[0] = xor3(z.w[0], e[q].x, e[q + 1].x);
+        z.w[1] = xor3(z.w[1], e[q].y, e[q + 1].y);
+        z.w[2] = xor3(z.w[2], e[q].z, e[q + 1].z);
+        z.w[3] = xor3(z.w[3], e[q].w, e[q + 1].w);
     }
-    return z;
 }
 
 __device__ __forceinline__ u4 xor4(const u4 &a, const u4 &b)

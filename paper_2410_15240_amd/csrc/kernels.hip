@@ -71,11 +71,11 @@ __device__ inline void build_tab4_row(const u4 &y, int p, Tab4 *out)
 }
 
 // Key setup in two launches. key_setup_kernel (one workgroup) runs the short
-// dependent chain: the AES-256 key expansion, H = AES_K(0), the squares H^(2^t)
-// and the powers H^8, H^16, ..., H^64. key_tables_kernel (many workgroups) then
-// builds every table from those: one wave per table of an odd multiple
-// H^(j 2^t) (j = 3, 5, 7), which forms its element from squares first, and one
-// table row or entry per thread for the others.
+// dependent chain: the AES-256 key expansion, H = AES_K(0) and the squares
+// H^(2^t). key_tables_kernel (many workgroups) then builds every table from those:
+// one wave per table of an odd multiple H^(j 2^t) (j = 3, 5, 7) or of a group
+// weight H^(8 k + 2), which forms its element from squares first, and one table
+// row or entry per thread for the others.
 //
 // Key-independent parts come from tables the compiler evaluates: the S-box and
 // T0, and the columns of the squaring map's powers S^k, k = 1..8.
@@ -113,7 +113,6 @@ __global__ __launch_bounds__(1024) void key_setup_kernel(SetupArgs a, KeyCtx *__
     __shared__ uint32_t s_t0[256];
     __shared__ uint32_t s_rk[60];
     __shared__ u4 s_hsq[kSquares];
-    __shared__ u4 s_h8k[8];
     const int tid = threadIdx.x;
     const uint32_t lane = tid & 63, wave = (uint32_t)tid >> 6;
 
@@ -155,18 +154,7 @@ __global__ __launch_bounds__(1024) void key_setup_kernel(SetupArgs a, KeyCtx *__
     __syncthreads();
 
     // Squares eight at a time: H^(2^(b + k)) = S^k(H^(2^b)), k = 1..8, one wave each,
-    // in four rounds. The tables need H^8, H^16, ..., H^64: four are squares, and
-    // the other four are products of them, formed by waves 0..2 during the rounds
-    // after the first (H^24 = H^16 . H^8, H^40 = H^32 . H^8, H^48 = H^32 . H^16,
-    // then H^56 = H^48 . H^8). A product by Y is one linear map whose columns the
-    // wave builds (Y . x^k for its lanes k and k + 64).
-    auto times = [&](const u4 &x, const u4 &y) {
-        const u4 yb = to_be(y);
-        WaveLinear mul;
-        mul.c0 = be_mul_xk_any(yb, (int)lane);
-        mul.c1 = be_mul_xk_any(yb, (int)lane + 64);
-        return from_be(mul.apply(to_be(x), lane));
-    };
+    // in four rounds.
     for (int r = 0; r < 4; ++r) {
         const int b = 8 * r;
         const int t = b + (int)(wave - kFrobWave0 + 1);
@@ -175,24 +163,7 @@ __global__ __launch_bounds__(1024) void key_setup_kernel(SetupArgs a, KeyCtx *__
             if (lane == 0)
                 s_hsq[t] = from_be(v);
         }
-        if (r == 1 && wave < 3) {   // H^24, H^40, H^48 (H^(2^t) for t <= 8 are in place)
-            const u4 x = s_hsq[wave == 2 ? 5 : 4 + (wave & 1)], y = s_hsq[wave == 2 ? 4 : 3];
-            const u4 prod = times(x, y);
-            if (lane == 0)
-                s_h8k[wave == 0 ? 2 : (wave == 1 ? 4 : 5)] = prod;
-        }
-        if (r == 2 && wave == 0) {   // H^56 = H^48 . H^8
-            const u4 prod = times(s_h8k[5], s_hsq[3]);
-            if (lane == 0)
-                s_h8k[6] = prod;
-        }
         __syncthreads();
-    }
-    if (tid < 8) {   // the squares among H^(8 (i + 1)): H^8, H^16, H^32, H^64
-        const int sq = tid == 0 ? 3 : (tid == 1 ? 4 : (tid == 3 ? 5 : (tid == 7 ? 6 : -1)));
-        const u4 v = sq >= 0 ? s_hsq[sq] : s_h8k[tid];
-        for (int j = 0; j < 4; ++j)
-            ctx->h8k[tid][j] = v.w[j];
     }
     for (int i = tid; i < kSquares; i += blockDim.x)
         for (int j = 0; j < 4; ++j)
@@ -203,13 +174,17 @@ __global__ __launch_bounds__(1024) void key_setup_kernel(SetupArgs a, KeyCtx *__
 // wave forms the element as a product of squares (H^(3 . 2^t) = H^(2^t) . H^(2^(t+1)),
 // H^(5 . 2^t) = H^(2^t) . H^(2^(t+2)), H^(7 . 2^t) = H^(3 . 2^t) . H^(2^(t+2))), each a
 // linear map whose columns the wave builds, and its lanes 0..31 write the table's
-// nibble positions. These waves come first, as they have the longest path. Then one
-// task per thread: a nibble position (16 entries) of the 4-bit tables of H and of
-// every H^(2^t), or one entry of the 8-bit positional tables of H^8, H^16, ..., H^64:
-// g16[i][v][k] = (byte v at byte k) . H^(8 (i + 1)), v's bit 7 = degree 8k.
+// nibble positions. Then in the same way one wave per group weight
+// H^(8 k + 2) = H^2 . H^8^k0 . H^16^k1 . H^32^k2, k = 1..7 (k0, k1, k2 the bits of k).
+// These waves come first, as they have the longest path. Then one task per thread: a
+// nibble position (16 entries) of the 4-bit tables of H, of every H^(2^t) and of
+// H^2 as grp_tab[0], or one entry of the 8-bit positional tables of H^16, H^32, H^64:
+// g16[i][v][k] = (byte v at byte k) . H^(16 . 2^i), v's bit 7 = degree 8k.
 constexpr uint32_t kOddThreads = kOddMul * kOddT * 64;
-constexpr uint32_t kTab4Tasks = (1 + kSquares) * kTab4Pos;
-constexpr uint32_t kTab8Entries = 8 * 16 * 256;
+constexpr uint32_t kGrpThreads = 7 * 64;
+constexpr uint32_t kWaveThreads = kOddThreads + kGrpThreads;
+constexpr uint32_t kTab4Tasks = (2 + kSquares) * kTab4Pos;
+constexpr uint32_t kTab8Entries = 3 * 16 * 256;
 constexpr uint32_t kTableThreads = 256;
 static_assert(kOddThreads % 64 == 0, "whole waves");
 
@@ -225,13 +200,23 @@ __device__ inline u4 times_wave(const u4 &x, const u4 &y, uint32_t lane)   // x 
 __global__ __launch_bounds__(kTableThreads) void key_tables_kernel(KeyCtx *__restrict__ ctx)
 {
     const uint32_t g = blockIdx.x * kTableThreads + threadIdx.x;
-    if (g < kOddThreads) {   // whole waves: the branch is uniform
+    if (g < kWaveThreads) {   // whole waves: the branch is uniform
         const uint32_t o = g >> 6, lane = g & 63;
         const uint32_t i = o / kOddT, t = o % kOddT;   // j = 2 i + 3
         auto sq = [&](uint32_t e) {   // H^(2^e); e = 32 only for the unused H^(5 . 2^30), H^(7 . 2^30)
             const uint32_t *y = ctx->hsq[min(e, (uint32_t)kSquares - 1)];
             return u4{{y[0], y[1], y[2], y[3]}};
         };
+        if (g >= kOddThreads) {
+            const uint32_t k = o - kOddThreads / 64 + 1;   // 1..7
+            u4 y = sq(1);
+            for (uint32_t b = 0; b < 3; ++b)
+                if ((k >> b) & 1u)
+                    y = times_wave(y, sq(3 + b), lane);
+            if (lane < kTab4Pos)
+                build_tab4_row(y, (int)lane, &ctx->grp_tab[k]);
+            return;
+        }
         u4 y = times_wave(sq(t), sq(t + (i == 1 ? 2u : 1u)), lane);
         if (i == 2)
             y = times_wave(y, sq(t + 2), lane);
@@ -239,18 +224,19 @@ __global__ __launch_bounds__(kTableThreads) void key_tables_kernel(KeyCtx *__res
             build_tab4_row(y, (int)lane, &ctx->odd_tab[i][t]);
         return;
     }
-    const uint32_t task = g - kOddThreads;
+    const uint32_t task = g - kWaveThreads;
     if (task < kTab4Tasks) {
         const uint32_t tbl = task / kTab4Pos, p = task % kTab4Pos;
-        const uint32_t *y = tbl == 0 ? ctx->h : ctx->hsq[tbl - 1];
-        build_tab4_row(u4{{y[0], y[1], y[2], y[3]}}, (int)p, tbl == 0 ? &ctx->h1_tab : &ctx->sq_tab[tbl - 1]);
+        const uint32_t *y = tbl == 0 ? ctx->h : (tbl <= kSquares ? ctx->hsq[tbl - 1] : ctx->hsq[1]);
+        Tab4 *out = tbl == 0 ? &ctx->h1_tab : (tbl <= kSquares ? &ctx->sq_tab[tbl - 1] : &ctx->grp_tab[0]);
+        build_tab4_row(u4{{y[0], y[1], y[2], y[3]}}, (int)p, out);
         return;
     }
     const uint32_t ent = task - kTab4Tasks;
     if (ent >= kTab8Entries)
         return;
     const uint32_t i = ent >> 12, k = (ent >> 8) & 15, v = ent & 255;
-    const uint32_t *hp = ctx->h8k[i];
+    const uint32_t *hp = ctx->hsq[4 + i];
     u4 b = be_mul_xk_any(to_be(u4{{hp[0], hp[1], hp[2], hp[3]}}), (int)(8 * k));   // degree 8k: v's bit 7
     u4 e = {{0u, 0u, 0u, 0u}};
     for (int bit = 7; bit >= 0; --bit) {
@@ -272,7 +258,7 @@ hipError_t launch_key_setup(const uint32_t key_words[8], KeyCtx *ctx, hipStream_
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    constexpr uint32_t kTasks = kOddThreads + kTab4Tasks + kTab8Entries;
+    constexpr uint32_t kTasks = kWaveThreads + kTab4Tasks + kTab8Entries;
     hipLaunchKernelGGL(key_tables_kernel, dim3((kTasks + kTableThreads - 1) / kTableThreads), dim3(kTableThreads), 0, s,
                        ctx);
     return hipGetLastError();
@@ -327,9 +313,9 @@ __device__ __forceinline__ ItemPos item_pos(const GcmLaunch &p, uint64_t item)
 // LDS layout (152 KiB + 1600 B, one 1024-thread workgroup per CU):
 //   [0, 64 KiB)        row x (256 B) = T0[x] for lanes 0..31 | T1[x] for lanes 0..31
 //   [64, 128 KiB)      the 8-bit table of H^L: entry (k, v) at 64 KiB + (v*16 + k)*16
-//   [128, 152 KiB)     4-bit tables of H^(2^t), t = 0..2 (8 KiB each): the first levels of
-//                      the lane-combine tree (the rest weights eight-lane group sums from
-//                      the key's tables in global memory)
+//   [128, 152 KiB)     4-bit tables of H^(2^t), t = 0..2 (8 KiB each): the three levels of
+//                      the lane combine (which then weights eight-lane group sums from the
+//                      key's tables in global memory)
 //   [152 KiB, +512 B)  per-wave segment partials and tag masks (workgroup tag combine)
 //   then 1 KiB         the tag masks of the workgroup's items when wave 0 computes them all
 //   then 64 B          per-wave progress counters (see the priority steps in the kernel)
@@ -348,18 +334,17 @@ __device__ __forceinline__ ItemPos item_pos(const GcmLaunch &p, uint64_t item)
 
 constexpr int kThreads = kGcmThreads;
 constexpr int kWavesPerWg = kGcmWavesPerWg;
-constexpr int kTreeTabs = 6;                 // H^(2^t), t = 0..5: lanes per item up to 64
-constexpr int kTreeLds = 3;                  // of which levels 0..2 in LDS (the AES modes)
+constexpr int kTreeLds = 3;                  // lane-combine tables H^(2^t), t = 0..2
 constexpr uint32_t kGhBase = 4096;           // uint4 index of the GHASH table (64 KiB)
 constexpr uint32_t kTreeBase = 8192;         // uint4 index of the tree tables (128 KiB)
 constexpr uint32_t kWgTagBase = (128 + 8 * kTreeLds) * 1024 / 16;   // uint4 index: 16 partials, 16 masks
 constexpr uint32_t kWgMaskBase = kWgTagBase + 32;                     // uint4 index: a tag mask per item (64)
 static_assert(kWavesPerWg <= 16 && kWavesPerWg % 4 == 0, "one workgroup-combine slot per wave");
 constexpr uint32_t kLdsBytes = (128 + 8 * kTreeLds) * 1024 + 512 + 1024 + 64;
-// Modes without data AES: the GHASH table, T0 (for the J0 masks) and all six tree tables.
+// Modes without data AES: the GHASH table, T0 (for the J0 masks) and the lane-combine tables.
 constexpr uint32_t kT0GhashOnly = 4096;         // uint4 index: 64 KiB
 constexpr uint32_t kTreeBaseGhashOnly = 4160;   // 65 KiB
-constexpr uint32_t kLdsGhashOnly = (65 + 8 * kTreeTabs) * 1024 + 64;
+constexpr uint32_t kLdsGhashOnly = (65 + 8 * kTreeLds) * 1024 + 64;
 // Per-wave progress counters (16 words): the last 64 B of either layout.
 constexpr uint32_t kProgBase = kLdsBytes / 4 - 16;
 constexpr uint32_t kProgBaseGhashOnly = kLdsGhashOnly / 4 - 16;
@@ -476,6 +461,79 @@ __device__ inline u4 group_mul_tab4(const u4 &x, const Tab4 *__restrict__ t, uin
     for (int w = 0; w < 4; ++w)
         r.w[w] = group_xor_sum<LL>(r.w[w]);
     return r;
+}
+
+// The sum of an item's lanes. Lane j's stream carries the weight H^(L+1-j) in its
+// segment (one H of it for the tag), so the item is sum_j acc_j H^(L-1-j) . H^2. Three
+// levels fold pairs, quads and eights: level t multiplies a group's left half sum by
+// H^(2^t) and adds the right half's. All 2^(t+1) lanes of a group share the product: the
+// left sum is broadcast to them by VALU cross-lane moves, lane i looks up its
+// 32 / 2^(t+1) consecutive nibble positions in the table in LDS, the lane that starts the
+// right half adds that half's sum, and the group XOR-sums its lanes. Then the group of
+// eight m (of M = L/8) multiplies its sum by H^(8 (M-1-m) + 2) in the same way, four
+// positions a lane, from the key's tables in global memory, and the item XOR-sums all its
+// lanes. Bound by latency: 16 + 8 + 4 lookups in LDS and 4 in global memory a lane in five
+// dependent batches. The form this replaces let one lane of each group look up all 32
+// positions (three levels, a last product by H^2: 128 LDS reads a wave in 16 batches, and
+// as the LDS serves a wave's 16-byte reads 16 lanes at a time, nearly as costly as with all
+// lanes active).
+template <int CTRL>
+__device__ __forceinline__ u4 dpp4(const u4 &x)
+{
+    u4 r;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+        r.w[w] = __builtin_amdgcn_update_dpp(0u, x.w[w], CTRL, 0xF, 0xF, false);
+    return r;
+}
+
+__device__ __forceinline__ uint32_t word_of(const u4 &x, uint32_t i)   // x.w[i], i differing between lanes
+{
+    const uint32_t lo = (i & 1u) ? x.w[1] : x.w[0], hi = (i & 1u) ? x.w[3] : x.w[2];
+    return (i & 2u) ? hi : lo;
+}
+
+template <int LL>
+__device__ __forceinline__ u4 lane_combine(const char *tree, const KeyCtx *__restrict__ c, u4 acc, uint32_t lane)
+{
+    u4 r = zero4();
+    {   // pairs: lane 0's sum . H + lane 1's
+        const uint32_t p = lane & 1;
+        const u4 x = dpp4<0xA0>(acc);   // quad_perm [0,0,2,2]
+        tab4_sum<8>(r, p ? x.w[2] : x.w[0], tree + p * 4096);
+        __builtin_amdgcn_sched_barrier(0);   // eight lookups in flight at a time: 32 VGPRs
+        tab4_sum<8>(r, p ? x.w[3] : x.w[1], tree + p * 4096 + 2048);
+        for (int w = 0; w < 4; ++w)
+            acc.w[w] = group_xor_sum<1>(p ? r.w[w] ^ acc.w[w] : r.w[w]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    {   // quads: the left pair's . H^2 + the right pair's
+        const uint32_t i = lane & 3;
+        r = zero4();
+        tab4_sum<8>(r, word_of(dpp4<0x00>(acc), i), tree + 8192 + i * 2048);   // quad_perm [0,0,0,0]
+        for (int w = 0; w < 4; ++w)
+            acc.w[w] = group_xor_sum<2>(i == 2 ? r.w[w] ^ acc.w[w] : r.w[w]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const uint32_t i = lane & 7;
+    {   // eights: the left quad's . H^4 + the right quad's
+        u4 x;
+        for (int w = 0; w < 4; ++w)   // row_half_mirror into the right quads only
+            x.w[w] = __builtin_amdgcn_update_dpp(acc.w[w], acc.w[w], 0x141, 0xF, 0xA, false);
+        r = zero4();
+        tab4_sum<4>(r, word_of(x, i >> 1) >> (16 * (i & 1)), tree + 16384 + i * 1024);
+        for (int w = 0; w < 4; ++w)
+            acc.w[w] = group_xor_sum<3>(i == 4 ? r.w[w] ^ acc.w[w] : r.w[w]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    constexpr uint32_t M = 1u << (LL - 3);
+    const uint32_t behind = M - 1 - ((lane >> 3) & (M - 1));   // groups of the item after this lane's
+    r = zero4();
+    tab4_sum<4>(r, word_of(acc, i >> 1) >> (16 * (i & 1)),
+                reinterpret_cast<const char *>(&c->grp_tab[behind]) + i * 1024);
+    for (int w = 0; w < 4; ++w)
+        acc.w[w] = group_xor_sum<LL>(r.w[w]);
+    return acc;
 }
 
 // AAD block u of a chain's AAD (zero-padded); one vector load when it is whole and aligned.
@@ -652,15 +710,14 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     constexpr uint32_t G = 64u >> LL;
     // Static, so its LDS address is a compile-time constant and a v_perm result
     // can be used as the ds_read address with no further add. Modes without
-    // data AES hold the GHASH table, a plain T0 (for the J0 masks) and all six
-    // lane-combine tables, 113 KiB.
+    // data AES hold the GHASH table, a plain T0 (for the J0 masks) and the
+    // lane-combine tables, 89 KiB.
     constexpr uint32_t kLdsUse = kAes ? kLdsBytes : kLdsGhashOnly;
     __shared__ uint4 lds4[kLdsUse / 16];
     const char *lds = reinterpret_cast<const char *>(lds4);
     constexpr uint32_t kGh = kAes ? kGhBase : 0u;                     // uint4 index of the GHASH table
     uint32_t *t0l = reinterpret_cast<uint32_t *>(lds4 + kT0GhashOnly);   // GHASH-only modes: T0 after the table
     constexpr uint32_t kTree = kAes ? kTreeBase : kTreeBaseGhashOnly;
-    constexpr int kTreeInLds = kAes ? kTreeLds : kTreeTabs;           // tree levels held in LDS
     const Tab4 *tree = reinterpret_cast<const Tab4 *>(lds4 + kTree);   // tree[t]: 4-bit table of H^(2^t)
     constexpr uint32_t kProg = kAes ? kProgBase : kProgBaseGhashOnly;
     const int tid = threadIdx.x;
@@ -694,9 +751,9 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
         if (tid < 16)   // slot 4 s + m: the m-th wave of SIMD s; slots no wave uses never hold anyone back
             reinterpret_cast<uint32_t *>(lds4)[kProg + tid] = (tid & 3) < kWavesPerWg / 4 ? 0u : 0xFFFFFFFFu;
         if (kGhash) {   // all loads of the 32 KiB GHASH table and the tree tables first, then the stores
-            const uint4 *g = reinterpret_cast<const uint4 *>(c->g16[(L >> 3) - 1]);
+            const uint4 *g = reinterpret_cast<const uint4 *>(c->g16[LL - 4]);
             const uint4 *sq = reinterpret_cast<const uint4 *>(c->sq_tab);
-            constexpr int kTreeU4 = kTreeInLds * (int)(sizeof(Tab4) / 16);
+            constexpr int kTreeU4 = kTreeLds * (int)(sizeof(Tab4) / 16);
             constexpr int kPer = (4096 + kThreads - 1) / kThreads;
             constexpr int kPerT = (kTreeU4 + kThreads - 1) / kThreads;
             uint4 gv[kPer], tv[kPerT];
@@ -1113,57 +1170,8 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
         iters_done += Ku;
         if constexpr (kGhash) {
             __builtin_amdgcn_s_setprio(3);   // the tail is a short latency-bound chain
-            // Lane j's stream carries the weight H^(L+1-j) in its segment (one H of it
-            // for the tag). sum_j acc_j H^(L-1-j) is a tree over the lanes: level t folds
-            // lane j + 2^t into lane j with the factor H^(2^t), every lane active at a
-            // level reading the same LDS table; then one multiply by H^2 in lane 0.
-            auto fold_in = [&](uint32_t lv) {   // lane j takes lane j + 2^lv's sum
-                u4 right;
-                for (int w = 0; w < 4; ++w) {
-                    const uint32_t x = acc.w[w];
-                    switch (lv) {   // uniform: the VALU cross-lane move for this distance
-                    case 0: right.w[w] = lane_down<1>(x); break;
-                    case 1: right.w[w] = lane_down<2>(x); break;
-                    case 2: right.w[w] = lane_down<4>(x); break;
-                    case 3: right.w[w] = lane_down<8>(x); break;
-                    case 4: right.w[w] = lane_down<16>(x); break;
-                    default: right.w[w] = lane_down<32>(x); break;
-                    }
-                }
-                return right;
-            };
-            constexpr uint32_t kLvLds = (uint32_t)LL < (uint32_t)kTreeInLds ? (uint32_t)LL : (uint32_t)kTreeInLds;
-#pragma unroll 1
-            for (uint32_t lv = 0; lv < kLvLds; ++lv) {
-                const u4 right = fold_in(lv);
-                if ((jl & ((2u << lv) - 1)) == 0)
-                    acc = xor4(mul_tab4_b8(acc, &tree[lv]), right);
-            }
-            if constexpr (kTreeInLds == 3) {
-                // After the three LDS levels, lane 8m of an item holds the sum C_m of its
-                // eight-lane group m (of M = L/8). The remaining levels would multiply these
-                // by H^8, H^16, H^32 one level after another; instead lane 8m multiplies C_m
-                // by its own weight H^(8 (M-1-m)) from the key's 8-bit tables in global
-                // memory (all groups at once, one multiply's latency), and the M products
-                // are XOR-folded into lane 0 by VALU cross-lane moves.
-                constexpr uint32_t M = L >> 3;
-                const uint32_t m = jl >> 3;
-                if ((jl & 7u) == 0 && m + 1 < M)   // M = 2: one group multiplies, by H^8 (a uniform table)
-                    acc = mul_tab8_b8(acc, reinterpret_cast<const uint4 *>(c->g16[M == 2 ? 0u : M - 2 - m]));
-                if constexpr (LL >= 6)
-                    for (int w = 0; w < 4; ++w)
-                        acc.w[w] ^= lane_down<32>(acc.w[w]);
-                if constexpr (LL >= 5)
-                    for (int w = 0; w < 4; ++w)
-                        acc.w[w] ^= lane_down<16>(acc.w[w]);
-                for (int w = 0; w < 4; ++w)
-                    acc.w[w] ^= lane_down<8>(acc.w[w]);
-            }
-            if (jl == 0)
-                acc = mul_tab4_b8(acc, &tree[1]);
-            if (SPLIT)   // the segment weights below take the sum in every lane of the group
-                for (int w = 0; w < 4; ++w)
-                    acc.w[w] = LL == 6 ? __builtin_amdgcn_readlane(acc.w[w], 0) : __shfl(acc.w[w], (int)(lane - jl), 64);
+            // The item's sum, in every lane of the item.
+            acc = lane_combine<LL>(reinterpret_cast<const char *>(tree), c, acc, lane);
             if (SPLIT) {
                 // A chain cut into S segments: segment s carries the weight
                 // H^((S-1-s) . 2^seg_log2) inside its chain, one multiply per nonzero

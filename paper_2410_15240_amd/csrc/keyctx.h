@@ -33,15 +33,16 @@ struct KeyCtx {
     uint32_t t0[256];           // T0[x] = {02}S(x) | S(x)<<8 | S(x)<<16 | {03}S(x)<<24
     uint8_t sbox[256];
     uint32_t h[4];              // H = AES_K(0^128)
-    uint32_t h8k[8][4];         // h8k[i] = H^(8 (i + 1)): H^8, H^16, ..., H^64
     uint32_t hsq[kSquares][4];        // hsq[t] = H^(2^t)
     Tab4 h1_tab;                // table of H
-    Tab4 sq_tab[kSquares];      // sq_tab[t]: table of H^(2^t) (t = 0..5 also combine the lanes of an item)
-    // 8-bit positional tables of H^8, H^16, ..., H^64, the 16 byte positions of one value
-    // side by side: g16[i][v][k] = (byte v at byte k) . H^(8 (i + 1)). g16[L/8 - 1] is the
-    // Horner multiplier H^L of L = 16, 32, 64 lanes per chain; g16[0..6] also weight the
-    // partial sums of an item's eight-lane groups at the end of the lane combine.
-    uint32_t g16[8][256][16][4];
+    Tab4 sq_tab[kSquares];      // sq_tab[t]: table of H^(2^t) (t = 0..2 also combine the lanes of an item)
+    // 8-bit positional tables of the Horner multipliers H^L of L = 16, 32, 64 lanes per item,
+    // the 16 byte positions of one value side by side:
+    // g16[i][v][k] = (byte v at byte k) . H^(16 . 2^i).
+    uint32_t g16[3][256][16][4];
+    // grp_tab[k]: table of H^(8 k + 2), the weight of an eight-lane group's sum with k groups
+    // behind it at the end of the lane combine (the two extra factors H belong to the tag).
+    Tab4 grp_tab[8];
     // A segment weight H^(m 2^g) is applied one nonzero base-8 digit d of m at a time:
     // H^(d 2^(g + 3i)) is a square for d = 1, 2, 4 and H^(j 2^t) with j = 3, 5, 7 otherwise
     // (6 = 3 . 2). odd_tab[i][t]: table of H^((2 i + 3) 2^t).
