@@ -41,7 +41,6 @@ int hip_fail(hipError_t e, const char *what)
 
 constexpr uint64_t kMaxChainBlocks = 0xFFFFFFFEull;   // GCM: at most 2^32 - 2 blocks per message
 constexpr size_t kMaxKeys = 8;
-constexpr int kMinSegLog2 = 8;                          // segments of >= 256 blocks (4 per lane)
 constexpr int kMinSmallSegLog2 = 7;                     // small launches: down to 128 blocks (2 per lane)
 constexpr uint64_t kMaxSmallSegs = 512;                 // ... with at most this many segments per chain
 constexpr int kMaxPipelineDepth = 8;                    // staging-ring slots
@@ -327,11 +326,38 @@ uint32_t ceil_log2(uint64_t x)
     return r;
 }
 
+// Estimated time of a uniform launch of n chains of qc blocks (the last of q_last), 2^ll
+// lanes per item and segments of 2^lg blocks, in iterations of a wave when all its CU's
+// waves are busy (3.6 us for decrypt + verify). With a share w of a CU's waves at work an
+// iteration takes 0.4 + 0.6 w of that (2.5 us at 8 of 16), as the waves share the LDS, but no
+// less than 0.58 (its dependent lookups, 2.1 us). Every wave-item adds its set-up and tail,
+// about one iteration. `slots` wave-items run at once; a last, partial pass is spread over
+// the CUs.
+double plan_cost(uint64_t n, uint64_t qc, uint64_t q_last, uint32_t ll, uint32_t lg, uint64_t slots)
+{
+    const uint64_t seg = 1ull << lg, L = 1ull << ll, g = 64u >> ll;
+    const uint64_t segs = (qc + seg - 1) >> lg;
+    const uint64_t it = ((seg < qc ? seg : qc) + L - 1) >> ll;                            // a full segment
+    const uint64_t it0 = (qc - (segs - 1) * seg + L - 1) >> ll;                             // segment 0
+    const uint64_t items = ((n - 1) * segs + ((q_last + seg - 1) >> lg) + g - 1) / g;       // wave-items
+    const double mean = (double)((segs - 1) * it + it0) / (double)segs;
+    const uint64_t full = items / slots, rest = items % slots;
+    const uint64_t cus = slots / kGcmWavesPerWg ? slots / kGcmWavesPerWg : 1;
+    double t = (double)full * (mean + 1.0);
+    if (rest) {
+        const double w = 0.4 + 0.6 * (double)((rest + cus - 1) / cus) / kGcmWavesPerWg;
+        t += (double)it * (w > 0.58 ? w : 0.58) + 1.0;
+    }
+    return t;
+}
+
 // Split `len` bytes (chains chain_base ..) into (chain, segment) work items and
-// pick the lanes per item. The aim is one item per resident wave-slot: short
-// chains get 16 or 32 lanes each (so one wave works on several chains and the
-// per-item lane combine is amortised over more blocks per lane); long chains
-// get 64 lanes and are cut into segments.
+// pick the lanes per item and the segment length with the least estimated time.
+// What that weighs: 16 or 32 lanes per item let one wave work on several short
+// chains, so that its set-up and tail are paid once for all of them; 64 lanes
+// and segments of few blocks give every wave work when the chains are few; and
+// wave-items that do not divide evenly over the waves leave a last pass in which
+// most of them idle.
 void make_plan(uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t slots, GcmLaunch &p)
 {
     const uint64_t n = (len + chain_bytes - 1) / chain_bytes;
@@ -342,21 +368,27 @@ void make_plan(uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t
     p.qc = (uint32_t)qc;
     p.last_len = len - (n - 1) * chain_bytes;
     p.q_last = (uint32_t)((p.last_len + 15) / 16);
-    uint32_t lg = ceil_log2(qc);
-    if (lg > 31)
-        lg = 31;
-    uint32_t ll = 0;
-    for (uint32_t cand = 4; cand <= 6; ++cand)
-        if (qc >= (4ull << cand) && ((n << cand) + 63) / 64 >= slots) {
-            ll = cand;
-            break;
-        }
-    if (ll == 0)   // short chains keep few lanes each; otherwise 64 lanes
-        ll = qc >= 256 ? 6 : (qc >= 128 ? 5 : 4);
+    uint32_t lg0 = ceil_log2(qc);
+    if (lg0 > 31)
+        lg0 = 31;
     auto items_at = [&](uint32_t g) { return n * ((qc + (1ull << g) - 1) >> g); };
-    if (ll == 6) {   // too few whole chains to fill the GPU: cut them into segments
-        while (lg > (uint32_t)kMinSegLog2 && items_at(lg) < slots)
-            --lg;
+    // Segments have at least 4 iterations. For each number of lanes the candidates run
+    // from whole chains to the first segment length with 8 wave-items per wave (shorter
+    // ones only add tails).
+    uint32_t ll = 6, lg = lg0;
+    double best = -1;
+    for (uint32_t l = 6; l >= 4; --l)
+        for (uint32_t g = lg0;; --g) {
+            const double c = plan_cost(n, qc, p.q_last, l, g, slots);
+            if (best < 0 || c < best) {
+                best = c;
+                ll = l;
+                lg = g;
+            }
+            if (g <= l + 2 || (items_at(g) << l) >= (slots * 8) << 6)
+                break;
+        }
+    if (ll == 6)
         // Small launches, where even 256-block segments leave more than half of the
         // waves idle: shorter segments, down to two iterations of the 64 lanes, while
         // a chain stays at most 512 segments (the tag sums and segment weights grow
@@ -367,17 +399,6 @@ void make_plan(uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t
         while (lg > (uint32_t)kMinSmallSegLog2 && items_at(lg) < slots / 2 &&
                ((qc + (1ull << (lg - 1)) - 1) >> (lg - 1)) <= kMaxSmallSegs)
             --lg;
-    } else {
-        // A few wave-items per wave that do not divide evenly leave some waves with
-        // one more than others: cut the chains until each wave has about 4 (segments
-        // of at least 4 iterations). Each item ends with a latency-bound tail (the
-        // lane combine, the segment weights), so more and shorter items cost more
-        // than the balance gains: 4 per wave measured ≈9% faster than 8, and than 2.
-        const uint64_t g = 64u >> ll;
-        auto wave_items = [&](uint32_t lgv) { return (items_at(lgv) + g - 1) / g; };
-        while (lg > ll + 2 && wave_items(lg) < 4 * slots && wave_items(lg) % slots != 0)
-            --lg;
-    }
     p.lanes_log2 = ll;
     p.seg_log2 = lg;
     p.segs_full = (uint32_t)((qc + (1ull << lg) - 1) >> lg);

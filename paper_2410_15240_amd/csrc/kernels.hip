@@ -790,10 +790,10 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
         rk[i] = kAes ? c->rk16[i] : 0u;
 
     const uint64_t nwaves = (uint64_t)gridDim.x * kWavesPerWg;
-    // A launch with fewer wave-items than resident waves numbers its waves across
-    // the workgroups first, which spreads the wave-items over all CUs; a full
-    // launch keeps each workgroup's waves on consecutive wave-items.
-    const bool spread = ((p.n_items + G - 1) / G) < nwaves;
+    // Unless every wave takes the same number of wave-items, waves are numbered across
+    // the workgroups first, which spreads a launch's only or last, partial pass of
+    // wave-items over all CUs; otherwise each workgroup's waves keep consecutive wave-items.
+    const bool spread = ((p.n_items + G - 1) / G) % nwaves != 0;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(spread ? (tid >> 6) * gridDim.x + blockIdx.x
                                                                 : blockIdx.x * kWavesPerWg + (tid >> 6));
     const uint64_t n_wave_items = (p.n_items + G - 1) / G;
@@ -902,11 +902,14 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
         if constexpr (!ENC && kGhash)
             if (valid && jl == 0 && (!SPLIT || (p.wg_tag && ip.s == 0)))
                 got = load16(p.tags_in + 16 * gchain);
-        // Iterations of this wave-item: uniform for uniform chains; for ragged chains
-        // the longest of the wave's segments (shorter ones are padded in front).
+        // Iterations of this wave-item: those of the longest of the wave's segments (shorter
+        // ones are padded in front). Whole uniform chains all take the same number; a
+        // segment 0 takes what its blocks need, not a full segment's iterations (40 MB of
+        // 625-block chains in segments of 512 and 113: 8 + 2 iterations instead of 8 + 8).
         uint32_t Ku = Ku_uniform;
-        if constexpr (RAG) {
-            Ku = wave_max_u32(valid ? (ip.e - ip.b + L - 1) >> LL : 0u);
+        if constexpr (RAG || SPLIT) {
+            const uint32_t own = valid ? (ip.e - ip.b + L - 1) >> LL : 0u;
+            Ku = LL == 6 ? __builtin_amdgcn_readfirstlane(own) : wave_max_u32(own);
         }
         uint32_t iv[3];
         chain_iv(p, gchain, iv);

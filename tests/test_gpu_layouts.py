@@ -1,0 +1,79 @@
+"""GPU parity where the work plan takes chains apart in its different ways.
+
+Each layout pins one way the planner lays a launch out on a 256-CU GPU: 16, 32 or
+64 lanes per item; whole chains or segments with a segment 0 shorter than the rest
+(which runs only the iterations its blocks need); one pass of wave-items, or
+several with a last one that leaves waves idle (their numbering spreads it over
+the CUs). The results are compared bit for bit with the CPU oracle: plaintext and
+flags with one tampered chain, ciphertext and tags, and the two modes that check
+tags without AES."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# length, chain bytes, AAD bytes, (lanes_log2, split, more than one pass)
+LAYOUTS = [
+    (16181855, 21728, 13, (4, 1, 0)),
+    (19440397, 2320, 1, (4, 1, 1)),
+    (13447333, 8208, 32, (5, 1, 0)),
+    (31839236, 18448, 0, (5, 1, 1)),
+    (15317645, 33664, 0, (6, 1, 0)),
+    (31792379, 17456, 13, (6, 1, 1)),
+    (12876048, 784, 0, (5, 0, 1)),
+    (35867559, 3888, 32, (6, 0, 1)),
+    (14959, 7248, 5, (6, 1, 0)),
+]
+
+
+@pytest.fixture(scope="module")
+def F():
+    import paper_2410_15240_amd as F
+    F.lib()
+    return F
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    import torch
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("length,chain,abytes,want", LAYOUTS)
+def test_layout_matches_the_oracle(F, length, chain, abytes, want):
+    out = (ctypes.c_uint64 * 7)()
+    assert F.lib().fastrack_plan(ctypes.c_uint64(length), ctypes.c_uint64(chain), ctypes.c_uint32(256), out) == 0
+    wave_items = -(-int(out[4]) // (64 >> int(out[0])))
+    assert (int(out[0]), int(out[6]), int(wave_items > 4096)) == want, list(out)
+    w = W.random_case(length % 1000, length, chain, aad_bytes=abytes)
+    aad = W.case_aad(w, chain) if abytes else None
+    d_aad = dev(aad) if abytes else None
+    ct, tags = oracle.chains_encrypt(w.key, w.base_iv, chain, w.payload, aad, abytes)
+    got_ct, got_tags = F.encrypt_tag(w.key, w.base_iv, chain, dev(w.payload), d_aad)
+    assert np.array_equal(host(got_tags), tags)
+    assert np.array_equal(host(got_ct), ct)
+    n = W.n_chains(length, chain)
+    W.flip_bit(ct[(n // 3) * chain:], 77)
+    pt, ok = oracle.chains_decrypt(w.key, w.base_iv, chain, ct, tags, aad, abytes)
+    assert ok.sum() == n - 1 and ok[n // 3] == 0
+    d_ct, d_tags = dev(ct), dev(tags)
+    got = F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags, d_aad)
+    assert np.array_equal(host(got[1]), ok)
+    assert np.array_equal(host(got[0]), pt)
+    e = F.decrypt_eager(w.key, w.base_iv, chain, d_ct, d_tags, d_aad)
+    assert e.rejected() == [n // 3]
+    assert np.array_equal(host(e.plaintext), pt)
+    ks = F.keystream(w.key, w.base_iv, chain, length)
+    got = F.apply_verify(w.key, w.base_iv, chain, d_ct, ks, d_tags, d_aad)
+    assert np.array_equal(host(got[1]), ok)
+    assert np.array_equal(host(got[0]), pt)
