@@ -487,10 +487,13 @@ __device__ __forceinline__ u4 dpp4(const u4 &x)
     return r;
 }
 
+// By value: a choice between elements of an array becomes an indexed load from memory.
+__device__ __forceinline__ uint32_t pick(bool b, uint32_t x, uint32_t y) { return b ? x : y; }
+
 __device__ __forceinline__ uint32_t word_of(const u4 &x, uint32_t i)   // x.w[i], i differing between lanes
 {
-    const uint32_t lo = (i & 1u) ? x.w[1] : x.w[0], hi = (i & 1u) ? x.w[3] : x.w[2];
-    return (i & 2u) ? hi : lo;
+    const uint32_t lo = pick(i & 1u, x.w[1], x.w[0]), hi = pick(i & 1u, x.w[3], x.w[2]);
+    return pick(i & 2u, hi, lo);
 }
 
 template <int LL>
@@ -500,9 +503,9 @@ __device__ __forceinline__ u4 lane_combine(const char *tree, const KeyCtx *__res
     {   // pairs: lane 0's sum . H + lane 1's
         const uint32_t p = lane & 1;
         const u4 x = dpp4<0xA0>(acc);   // quad_perm [0,0,2,2]
-        tab4_sum<8>(r, p ? x.w[2] : x.w[0], tree + p * 4096);
+        tab4_sum<8>(r, pick(p, x.w[2], x.w[0]), tree + p * 4096);
         __builtin_amdgcn_sched_barrier(0);   // eight lookups in flight at a time: 32 VGPRs
-        tab4_sum<8>(r, p ? x.w[3] : x.w[1], tree + p * 4096 + 2048);
+        tab4_sum<8>(r, pick(p, x.w[3], x.w[1]), tree + p * 4096 + 2048);
         for (int w = 0; w < 4; ++w)
             acc.w[w] = group_xor_sum<1>(p ? r.w[w] ^ acc.w[w] : r.w[w]);
         __builtin_amdgcn_sched_barrier(0);
