@@ -311,8 +311,8 @@ __device__ __forceinline__ ItemPos item_pos(const GcmLaunch &p, uint64_t item)
 // ===========================================================================
 //
 // LDS layout (152 KiB + 1600 B, one 1024-thread workgroup per CU):
-//   [0, 64 KiB)        row x (256 B) = T0[x] for lanes 0..31 | T1[x] for lanes 0..31
-//   [64, 128 KiB)      the 8-bit table of H^L: entry (k, v) at 64 KiB + (v*16 + k)*16
+//   [0, 64 KiB)        the 8-bit table of H^L: entry (k, v) at (v*16 + k)*16
+//   [64, 128 KiB)      row x (256 B) = T0[x] for lanes 0..31 | T1[x] for lanes 0..31
 //   [128, 152 KiB)     4-bit tables of H^(2^t), t = 0..2 (8 KiB each): the three levels of
 //                      the lane combine (which then weights eight-lane group sums from the
 //                      key's tables in global memory)
@@ -325,22 +325,28 @@ __device__ __forceinline__ ItemPos item_pos(const GcmLaunch &p, uint64_t item)
 // hold the tables the lane combine needs. Lanes l and l+32 share a copy: the LDS
 // serves a wave's 32-bit reads 32 lanes at a time, so the 32 copies make every
 // lookup conflict-free. A T0/T1 address is one v_perm_b32: byte 0 = (lane%32)*4 +
-// 128*table, byte 1 = the state byte, bytes 2..3 = 0.
+// 128*table, byte 1 = the state byte, bytes 2..3 = 1, 0 (the tables' place at 64 KiB);
+// for byte 1 of the state, already in place, it is a three-input logic op on vector
+// registers alone, which issues at almost twice the rate (0.65 against 1.05 CU-cycles).
 // GHASH multiplies by H^L as X . H^L = sum_k E_k[x_k] over the 16 byte positions k.
 // The 16 entries of one byte value sit side by side in a 256-byte row, so position
 // k lies in the k-th 16-byte bank group. The LDS serves a wave's 16-byte reads 16
 // lanes at a time; lane l takes position k = j xor (l mod 16) at lookup j, so the 16
-// lanes served together always hit 16 different bank groups, whatever the data.
+// lanes served together always hit 16 different bank groups, whatever the data. The
+// table starts at LDS address 0, so such an address, v << 8 | k << 4, is one v_perm_b32
+// of the value byte and a lane constant.
 
 constexpr int kThreads = kGcmThreads;
 constexpr int kWavesPerWg = kGcmWavesPerWg;
 constexpr int kTreeLds = 3;                  // lane-combine tables H^(2^t), t = 0..2
-constexpr uint32_t kGhBase = 4096;           // uint4 index of the GHASH table (64 KiB)
+constexpr uint32_t kGhBase = 0;              // uint4 index of the GHASH table
+constexpr uint32_t kTBase = 4096;            // uint4 index of T0 | T1 (64 KiB)
 constexpr uint32_t kTreeBase = 8192;         // uint4 index of the tree tables (128 KiB)
 constexpr uint32_t kWgTagBase = (128 + 8 * kTreeLds) * 1024 / 16;   // uint4 index: 16 partials, 16 masks
 constexpr uint32_t kWgMaskBase = kWgTagBase + 32;                     // uint4 index: a tag mask per item (64)
 static_assert(kWavesPerWg <= 16 && kWavesPerWg % 4 == 0, "one workgroup-combine slot per wave");
 constexpr uint32_t kLdsBytes = (128 + 8 * kTreeLds) * 1024 + 512 + 1024 + 64;
+static_assert(kTBase * 16 == 0x10000, "one address byte places the T tables");
 // Modes without data AES: the GHASH table, T0 (for the J0 masks) and the lane-combine tables.
 constexpr uint32_t kT0GhashOnly = 4096;         // uint4 index: 64 KiB
 constexpr uint32_t kTreeBaseGhashOnly = 4160;   // 65 KiB
@@ -363,24 +369,38 @@ __device__ __forceinline__ uint32_t tlk(const char *lds, uint32_t word, uint32_t
     return *reinterpret_cast<const uint32_t *>(lds + __builtin_amdgcn_perm(word, lanec, sel));
 }
 
+// The same for byte 1 of the word, which is in its place: (word & 0xFF00) | lanec, with the
+// mask in a vector register (with a scalar operand the op would issue at the lower rate).
+__device__ __forceinline__ uint32_t tlk1(const char *lds, uint32_t word, uint32_t lanec, uint32_t mask)
+{
+    return *reinterpret_cast<const uint32_t *>(lds + __builtin_amdgcn_bitop3_b32(word, mask, lanec, 0xEA));
+}
+
+__device__ __forceinline__ uint32_t byte1_mask()
+{
+    uint32_t m;
+    asm("v_mov_b32 %0, 0xff00" : "=v"(m));   // opaque, so that it stays in a vector register
+    return m;
+}
+
 __device__ __forceinline__ uint32_t rotl16(uint32_t x) { return __builtin_amdgcn_alignbit(x, x, 16); }
 
 // One output column of an AES round, T0[a.b0] ^ T1[b.b1] ^ T2[c.b2] ^ T3[d.b3] ^ k,
 // with kr = rotl16(k): only T0 and T1 are in LDS.
 __device__ __forceinline__ uint32_t tcol(const char *lds, uint32_t a, uint32_t b, uint32_t c, uint32_t d,
-                                         uint32_t kr, uint32_t lc0, uint32_t lc1)
+                                         uint32_t kr, uint32_t lc0, uint32_t lc1, uint32_t m1)
 {
     const uint32_t u = xor3(tlk(lds, c, lc0, FT_SEL(2)), tlk(lds, d, lc1, FT_SEL(3)), kr);
-    return xor3(tlk(lds, a, lc0, FT_SEL(0)), tlk(lds, b, lc1, FT_SEL(1)), rotl16(u));
+    return xor3(tlk(lds, a, lc0, FT_SEL(0)), tlk1(lds, b, lc1, m1), rotl16(u));
 }
 
 // Final round column, S(a.b0) | S(b.b1) << 8 | S(c.b2) << 16 | S(d.b3) << 24, XOR k:
 // S(x) is byte 1 of T0[x] and byte 2 of T1[x].
 __device__ __forceinline__ uint32_t tlast(const char *lds, uint32_t a, uint32_t b, uint32_t c, uint32_t d,
-                                          uint32_t k, uint32_t lc0, uint32_t lc1)
+                                          uint32_t k, uint32_t lc0, uint32_t lc1, uint32_t m1)
 {
     const uint32_t a0 = tlk(lds, a, lc0, FT_SEL(0));
-    const uint32_t a1 = tlk(lds, b, lc1, FT_SEL(1));
+    const uint32_t a1 = tlk1(lds, b, lc1, m1);
     const uint32_t a2 = tlk(lds, c, lc0, FT_SEL(2));
     const uint32_t a3 = tlk(lds, d, lc1, FT_SEL(3));
     return xor3(__builtin_amdgcn_perm(a1, a0, 0x0C0C0601u), __builtin_amdgcn_perm(a3, a2, 0x06010C0Cu), k);
@@ -629,70 +649,78 @@ struct NoAadSteps {
 // AES-256 of one block x (before the first AddRoundKey) with the streaming
 // kernel's LDS T-tables: every lane encrypts its own block. rk holds the round
 // keys of rounds 1..13 rotated by 16 bits (rk[4..55]), the others as they are.
-__device__ inline u4 aes_block_lds(const char *lds, const uint32_t *rk, const u4 &x, uint32_t lc0, uint32_t lc1)
+__device__ inline u4 aes_block_lds(const char *lds, const uint32_t *rk, const u4 &x, uint32_t lc0, uint32_t lc1,
+                                   uint32_t m1)
 {
     uint32_t s0 = x.w[0] ^ rk[0], s1 = x.w[1] ^ rk[1], s2 = x.w[2] ^ rk[2], s3 = x.w[3] ^ rk[3];
 #pragma unroll
     for (int r = 1; r < 14; ++r) {
-        const uint32_t n0 = tcol(lds, s0, s1, s2, s3, rk[4 * r + 0], lc0, lc1);
-        const uint32_t n1 = tcol(lds, s1, s2, s3, s0, rk[4 * r + 1], lc0, lc1);
-        const uint32_t n2 = tcol(lds, s2, s3, s0, s1, rk[4 * r + 2], lc0, lc1);
-        const uint32_t n3 = tcol(lds, s3, s0, s1, s2, rk[4 * r + 3], lc0, lc1);
+        const uint32_t n0 = tcol(lds, s0, s1, s2, s3, rk[4 * r + 0], lc0, lc1, m1);
+        const uint32_t n1 = tcol(lds, s1, s2, s3, s0, rk[4 * r + 1], lc0, lc1, m1);
+        const uint32_t n2 = tcol(lds, s2, s3, s0, s1, rk[4 * r + 2], lc0, lc1, m1);
+        const uint32_t n3 = tcol(lds, s3, s0, s1, s2, rk[4 * r + 3], lc0, lc1, m1);
         s0 = n0; s1 = n1; s2 = n2; s3 = n3;
     }
     u4 o;
-    o.w[0] = tlast(lds, s0, s1, s2, s3, rk[56], lc0, lc1);
-    o.w[1] = tlast(lds, s1, s2, s3, s0, rk[57], lc0, lc1);
-    o.w[2] = tlast(lds, s2, s3, s0, s1, rk[58], lc0, lc1);
-    o.w[3] = tlast(lds, s3, s0, s1, s2, rk[59], lc0, lc1);
+    o.w[0] = tlast(lds, s0, s1, s2, s3, rk[56], lc0, lc1, m1);
+    o.w[1] = tlast(lds, s1, s2, s3, s0, rk[57], lc0, lc1, m1);
+    o.w[2] = tlast(lds, s2, s3, s0, s1, rk[58], lc0, lc1, m1);
+    o.w[3] = tlast(lds, s3, s0, s1, s2, rk[59], lc0, lc1, m1);
     return o;
 }
 
-// acc . H^L xor g with the 8-bit table of H^L in LDS: byte positions 0..7
-// directly, 8..15 through x^64.
 // The lane constants of the GHASH lookups: l = lane mod 16.
 struct GhLane {
-    uint32_t sel;   // v_perm selector: byte b <- byte b xor (l mod 4) of this word (l & 4: of the paired word)
-    uint32_t row;   // (l << 4) | the table's LDS byte address
-    bool swap;      // l & 8: words 0,1 <-> 2,3
+    uint32_t sel;      // v_perm selector: byte b <- byte b xor (l mod 4) of this word (l & 4: of the paired word)
+    uint32_t swap;     // all ones if l & 8: words 0,1 <-> 2,3
+    uint32_t row[4];   // byte j mod 4 of word j / 4: (j xor l) << 4
 };
 
-__device__ __forceinline__ GhLane ghash_lane(uint32_t lane, uint32_t table_bytes)
+__device__ __forceinline__ GhLane ghash_lane(uint32_t lane)
 {
     const uint32_t l = lane & 15;
     GhLane k;
     k.sel = 0u;
     for (uint32_t b = 0; b < 4; ++b)
         k.sel |= ((b ^ (l & 3)) + (l & 4)) << (8 * b);
-    k.row = (l << 4) | table_bytes;
-    k.swap = (l & 8) != 0;
+    k.swap = (l & 8) ? 0xFFFFFFFFu : 0u;
+    for (uint32_t w = 0; w < 4; ++w)
+        k.row[w] = (0x30201000u + w * 0x40404040u) ^ (l * 0x10101010u);
     return k;
 }
 
-// Horner step acc . H^L xor g: the bytes of acc are permuted so that byte j of p is
-// byte j xor l of acc; lookup j then reads position j xor l, whose entry for value
-// v is at row v, column (j xor l) of the table: address (v << 8 | row) xor (j << 4).
+// Horner step acc . H^L xor g with the 8-bit table of H^L at lds: the bytes of acc are
+// permuted so that byte j of p is byte j xor l of acc; lookup j then reads position j xor l,
+// whose entry for value v is at row v, column (j xor l) of the table: v << 8 | (j xor l) << 4.
+// g comes in with the last entry, so the lookups wait for acc alone.
 __device__ __forceinline__ u4 ghash_step(const char *lds, const u4 &acc, const u4 &g, const GhLane &k)
 {
     uint32_t q[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w)
         q[w] = __builtin_amdgcn_perm(acc.w[w ^ 1], acc.w[w], k.sel);
-    const uint32_t p[4] = {k.swap ? q[2] : q[0], k.swap ? q[3] : q[1], k.swap ? q[0] : q[2], k.swap ? q[1] : q[3]};
-    u4 r = g;
+    uint32_t p[4];
 #pragma unroll
-    for (int j = 0; j < 16; j += 2) {
-        // byte j of p into bits 8..15 (v_perm selector 0x0C: a zero byte)
-        const uint32_t v0 = __builtin_amdgcn_perm(0u, p[j >> 2], 0x0C0C000Cu | ((uint32_t)(j & 3) << 8));
-        const uint32_t v1 = __builtin_amdgcn_perm(0u, p[(j + 1) >> 2], 0x0C0C000Cu | ((uint32_t)((j + 1) & 3) << 8));
-        const uint4 ea = *reinterpret_cast<const uint4 *>(lds + ((v0 | k.row) ^ ((uint32_t)j << 4)));
-        const uint4 eb = *reinterpret_cast<const uint4 *>(lds + ((v1 | k.row) ^ ((uint32_t)(j + 1) << 4)));
+    for (int w = 0; w < 4; ++w)   // swap ? q[w ^ 2] : q[w]
+        p[w] = __builtin_amdgcn_bitop3_b32(k.swap, q[w ^ 2], q[w], 0xCA);
+    auto entry = [&](int j) {   // byte j of p into bits 8..15, its column into bits 4..7
+        const uint32_t b = (uint32_t)(j & 3);
+        const uint32_t at = __builtin_amdgcn_perm(k.row[j >> 2], p[j >> 2], 0x0C0C0004u + b + (b << 8));
+        return *reinterpret_cast<const uint4 *>(lds + at);
+    };
+    const uint4 e0 = entry(0), e1 = entry(1), e2 = entry(2);
+    u4 r = {{xor3(e0.x, e1.x, e2.x), xor3(e0.y, e1.y, e2.y), xor3(e0.z, e1.z, e2.z), xor3(e0.w, e1.w, e2.w)}};
+#pragma unroll
+    for (int j = 3; j < 15; j += 2) {
+        const uint4 ea = entry(j), eb = entry(j + 1);
         r.w[0] = xor3(r.w[0], ea.x, eb.x);
         r.w[1] = xor3(r.w[1], ea.y, eb.y);
         r.w[2] = xor3(r.w[2], ea.z, eb.z);
         r.w[3] = xor3(r.w[3], ea.w, eb.w);
     }
-    return r;
+    const uint4 el = entry(15);
+    return u4{{xor3(r.w[0], el.x, g.w[0]), xor3(r.w[1], el.y, g.w[1]), xor3(r.w[2], el.z, g.w[2]),
+               xor3(r.w[3], el.w, g.w[3])}};
 }
 
 // Lanes per item L = 2^LL. Item slot g of a wave (lanes g*L .. g*L+L-1) takes
@@ -718,7 +746,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     constexpr uint32_t kLdsUse = kAes ? kLdsBytes : kLdsGhashOnly;
     __shared__ uint4 lds4[kLdsUse / 16];
     const char *lds = reinterpret_cast<const char *>(lds4);
-    constexpr uint32_t kGh = kAes ? kGhBase : 0u;                     // uint4 index of the GHASH table
+    constexpr uint32_t kGh = kGhBase;                                 // uint4 index of the GHASH table
     uint32_t *t0l = reinterpret_cast<uint32_t *>(lds4 + kT0GhashOnly);   // GHASH-only modes: T0 after the table
     constexpr uint32_t kTree = kAes ? kTreeBase : kTreeBaseGhashOnly;
     const Tab4 *tree = reinterpret_cast<const Tab4 *>(lds4 + kTree);   // tree[t]: 4-bit table of H^(2^t)
@@ -734,7 +762,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
             // Pass k of a wave writes the 64 words (w + k W) * 64 + [0, 64) of region
             // (w + k W) / 256, all from one T0 row: lane k fetches that row up front
             // and each pass broadcasts it, so no pass waits on memory.
-            uint32_t *t = reinterpret_cast<uint32_t *>(lds4);
+            uint32_t *t = reinterpret_cast<uint32_t *>(lds4 + kTBase);
             constexpr uint32_t kPasses = (16384 + kThreads - 1) / kThreads;
             static_assert(kPasses <= 64, "one T0 row per lane and pass");
             const uint32_t w = (uint32_t)tid >> 6;
@@ -778,9 +806,10 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     }
     __syncthreads();
 
-    const uint32_t lb = (lane & 31) << 2;
+    const uint32_t lb = ((lane & 31) << 2) | (kTBase * 16);
     const uint32_t lc0 = lb, lc1 = lb | 0x80u;
-    const GhLane gk = ghash_lane(lane, kGh * 16);
+    const uint32_t m1 = byte1_mask();
+    const GhLane gk = ghash_lane(lane);
     // The 60 round-key words are uniform: they stay in scalar registers (the XORs
     // take them as scalar operands), which keeps the kernel within the 128 VGPRs
     // that four waves per SIMD allow. Rounds 1..13 use them rotated by 16 bits (the
@@ -851,7 +880,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
             }
             u4 e;
             if constexpr (kAes)
-                e = aes_block_lds(lds, rk, j0, lc0, lc1);
+                e = aes_block_lds(lds, rk, j0, lc0, lc1, m1);
             else
                 e = aes256_encrypt_tt(j0, c->rk, [&](uint32_t x) { return t0l[x]; });
             m = xor4(e, lenh);
@@ -910,7 +939,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
         // segment 0 takes what its blocks need, not a full segment's iterations (40 MB of
         // 625-block chains in segments of 512 and 113: 8 + 2 iterations instead of 8 + 8).
         uint32_t Ku = Ku_uniform;
-        if constexpr (RAG || SPLIT) {
+        if constexpr (RAG || SPLIT || !kGhash) {   // (modes without GHASH run segments with SPLIT unset)
             const uint32_t own = valid ? (ip.e - ip.b + L - 1) >> LL : 0u;
             Ku = LL == 6 ? __builtin_amdgcn_readfirstlane(own) : wave_max_u32(own);
         }
@@ -1010,6 +1039,37 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
             gq = ctr >> 8;
         };
         const uint32_t k3 = rk[3] >> 24;   // key byte that meets the counter's low byte
+        // The keystream block of counter block IV_i || [t + 2]_32 (data blocks start at
+        // inc32(J0)) XOR d; `active`: the lane has a block.
+        auto aes_xor = [&](uint32_t t, bool active, const u4 &d) {
+            const uint32_t ctr = t + 2u;
+            const bool stale = active && (ctr >> 8) != gq;
+            if (__ballot(stale))
+                if (stale)
+                    group_setup(ctr);
+            // Round 1, column 0 (T3 of the counter's low byte), then round 2 on the
+            // cached sums: each output column adds its one lookup of column 0.
+            const uint32_t c0 = p0 ^ rotl16(tlk(lds, ctr ^ k3, lc1, FT_SEL(0)));
+            uint32_t s0 = q0 ^ tlk(lds, c0, lc0, FT_SEL(0));
+            uint32_t s1 = q1 ^ rotl16(tlk(lds, c0, lc1, FT_SEL(3)));
+            uint32_t s2 = q2 ^ rotl16(tlk(lds, c0, lc0, FT_SEL(2)));
+            uint32_t s3 = q3 ^ tlk(lds, c0, lc1, FT_SEL(1));
+#pragma unroll
+            for (int r = 3; r < 14; ++r) {
+                const uint32_t n0 = tcol(lds, s0, s1, s2, s3, rk[4 * r + 0], lc0, lc1, m1);
+                const uint32_t n1 = tcol(lds, s1, s2, s3, s0, rk[4 * r + 1], lc0, lc1, m1);
+                const uint32_t n2 = tcol(lds, s2, s3, s0, s1, rk[4 * r + 2], lc0, lc1, m1);
+                const uint32_t n3 = tcol(lds, s3, s0, s1, s2, rk[4 * r + 3], lc0, lc1, m1);
+                s0 = n0; s1 = n1; s2 = n2; s3 = n3;
+            }
+            // Final round, XOR the data.
+            u4 o;
+            o.w[0] = tlast(lds, s0, s1, s2, s3, rk[56] ^ d.w[0], lc0, lc1, m1);
+            o.w[1] = tlast(lds, s1, s2, s3, s0, rk[57] ^ d.w[1], lc0, lc1, m1);
+            o.w[2] = tlast(lds, s2, s3, s0, s1, rk[58] ^ d.w[2], lc0, lc1, m1);
+            o.w[3] = tlast(lds, s3, s0, s1, s2, rk[59] ^ d.w[3], lc0, lc1, m1);
+            return o;
+        };
         // Iteration k on the loaded data block d (and keystream block kv for kApplyKs).
         // AAD: whether iteration k may hold AAD blocks (k <= kmax); a step built
         // without them issues a fixed set of memory accesses.
@@ -1017,32 +1077,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
             const uint32_t t = q.t;
             u4 o;
             if constexpr (kAes) {
-                // Counter block IV_i || [t + 2]_32 (data blocks start at inc32(J0)).
-                const uint32_t ctr = t + 2u;
-                const bool stale = q.active && (ctr >> 8) != gq;
-                if (__ballot(stale))
-                    if (stale)
-                        group_setup(ctr);
-                // Round 1, column 0 (T3 of the counter's low byte), then round 2 on the
-                // cached sums: each output column adds its one lookup of column 0.
-                const uint32_t c0 = p0 ^ rotl16(tlk(lds, ctr ^ k3, lc1, FT_SEL(0)));
-                uint32_t s0 = q0 ^ tlk(lds, c0, lc0, FT_SEL(0));
-                uint32_t s1 = q1 ^ rotl16(tlk(lds, c0, lc1, FT_SEL(3)));
-                uint32_t s2 = q2 ^ rotl16(tlk(lds, c0, lc0, FT_SEL(2)));
-                uint32_t s3 = q3 ^ tlk(lds, c0, lc1, FT_SEL(1));
-#pragma unroll
-                for (int r = 3; r < 14; ++r) {
-                    const uint32_t n0 = tcol(lds, s0, s1, s2, s3, rk[4 * r + 0], lc0, lc1);
-                    const uint32_t n1 = tcol(lds, s1, s2, s3, s0, rk[4 * r + 1], lc0, lc1);
-                    const uint32_t n2 = tcol(lds, s2, s3, s0, s1, rk[4 * r + 2], lc0, lc1);
-                    const uint32_t n3 = tcol(lds, s3, s0, s1, s2, rk[4 * r + 3], lc0, lc1);
-                    s0 = n0; s1 = n1; s2 = n2; s3 = n3;
-                }
-                // Final round, XOR the data.
-                o.w[0] = tlast(lds, s0, s1, s2, s3, rk[56] ^ d.w[0], lc0, lc1);
-                o.w[1] = tlast(lds, s1, s2, s3, s0, rk[57] ^ d.w[1], lc0, lc1);
-                o.w[2] = tlast(lds, s2, s3, s0, s1, rk[58] ^ d.w[2], lc0, lc1);
-                o.w[3] = tlast(lds, s3, s0, s1, s2, rk[59] ^ d.w[3], lc0, lc1);
+                o = aes_xor(t, q.active, d);
             } else if constexpr (MODE == kApplyKs) {
                 o = xor4(d, kv);
             } else {
@@ -1166,11 +1201,47 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
                 }
             }
         } else {
-            for (uint32_t k = 0; k < Ku; ++k) {
-                pace(k);
-                const Slot q = slot_of(k);
-                process(AadSteps{}, k, q, kRead ? load_block(src, q) : zero4(),
-                        MODE == kApplyKs ? load_block(ksrc, q) : zero4());
+            // Iterations k_a <= k < k_b hold a whole block in every lane and no AAD: they
+            // take no branches, so the scheduler mixes the GHASH lookups into the AES
+            // rounds (the product acc . H^L waits for nothing in the iteration) and the load
+            // of d has the whole iteration to arrive. The others, at the ends of a segment,
+            // are taken one at a time with every check.
+            uint32_t k_a = Ku, k_b = Ku;
+            if constexpr (kAes) {
+                const int first = pad - (int)jl;   // the lane's first block is in iteration ceil(first / L)
+                const uint32_t a = !valid ? Ku : (first > 0 ? (uint32_t)(first + (int)L - 1) >> LL : 0u);
+                k_a = max(LL == 6 ? (pad > 0 ? (uint32_t)(pad + (int)L - 1) >> LL : 0u) : wave_max_u32(a),
+                          (uint32_t)(kmax + 1));
+                if constexpr (LL == 6)
+                    k_a = __builtin_amdgcn_readfirstlane(valid ? k_a : Ku);
+                if (__ballot(valid && tail != 0 && ip.e == ip.q))
+                    k_b = Ku - 1;
+            }
+            for (uint32_t k = 0; k < Ku;) {
+                if (kAes && k >= k_a && k < k_b) {
+                    uint32_t t = ip.b + (uint32_t)((int)(k << LL) + (int)jl - pad);
+                    do {
+                        pace(k);
+                        v4u dv = {0u, 0u, 0u, 0u};
+                        if constexpr (kRead)
+                            dv = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(src) + t);
+                        const u4 d = {{dv.x, dv.y, dv.z, dv.w}};
+                        const u4 o = aes_xor(t, true, d);
+                        if constexpr (kWrite) {
+                            const v4u ov = {o.w[0], o.w[1], o.w[2], o.w[3]};
+                            __builtin_nontemporal_store(ov, reinterpret_cast<v4u *>(dst) + t);
+                        }
+                        if constexpr (kGhash)
+                            acc = ghash_step(lds, acc, ENC ? o : d, gk);
+                        t += L;
+                    } while (++k < k_b);
+                } else {
+                    pace(k);
+                    const Slot q = slot_of(k);
+                    process(AadSteps{}, k, q, kRead ? load_block(src, q) : zero4(),
+                            MODE == kApplyKs ? load_block(ksrc, q) : zero4());
+                    ++k;
+                }
             }
         }
         iters_done += Ku;
@@ -1333,7 +1404,7 @@ __global__ __launch_bounds__(256) void seq_ghash_kernel(GcmLaunch p)
     if (chain >= p.n_chains)
         return;
     const char *lds = reinterpret_cast<const char *>(s_tab);
-    const GhLane gk = ghash_lane(threadIdx.x & 63, 0u);
+    const GhLane gk = ghash_lane(threadIdx.x & 63);
     auto mul_h = [&](const u4 &x) { return ghash_step(lds, x, zero4(), gk); };   // x . H
     const uint64_t gchain = p.chain_base + chain;
     const bool last = chain == p.n_chains - 1;
