@@ -97,6 +97,8 @@ def _check(rc):
 
 
 def _host_bytes(x, n, what):
+    if type(x) is bytes and len(x) == n:   # ctypes passes the address of an immutable object's bytes
+        return x
     if isinstance(x, _torch.Tensor):
         x = x.detach().to("cpu", _torch.uint8).contiguous().numpy().tobytes()
     elif not isinstance(x, (bytes, bytearray)):
@@ -136,6 +138,52 @@ def _u8(t, what, numel=None, min_numel=None, cuda=True, device=None, pinned=Fals
         if pinned and not t.is_pinned():
             raise ValueError("%s must be in pinned host memory" % what)
     return t
+
+
+# A small call spends more time here than on the GPU (12 of 18 us a call before, 4 now), so
+# the calls check each tensor in one expression and fall back to _u8 for the message; the
+# device is entered only when it is not the current one, and the stream handle is read
+# without building a stream object.
+_Tensor, _uint8 = _torch.Tensor, _torch.uint8
+
+
+def _dev_ptr(t, what, numel, idx, device):
+    """The address of a caller's buffer: a contiguous uint8 tensor of numel bytes on device idx."""
+    if not (isinstance(t, _Tensor) and t.dtype is _uint8 and t.numel() == numel and t.is_contiguous()
+            and t.get_device() == idx):
+        _u8(t, what, numel=numel, device=device)
+    return t.data_ptr()
+
+
+def _dev_aad(aad, n, idx, device):
+    """(address, bytes per chain) of the AAD of an n-chain call."""
+    if aad is None:
+        return None, 0
+    if isinstance(aad, _Tensor) and aad.dtype is _uint8 and aad.is_contiguous() and aad.get_device() == idx:
+        m = aad.numel()
+        if n > 0 and m % n == 0 and m // n <= 0xFFFFFFFF:
+            return aad.data_ptr(), m // n
+    aad_bytes = _aad_bytes(aad, n, device=device)
+    return aad.data_ptr(), aad_bytes
+
+
+def _chains(length, chain_bytes):
+    if type(chain_bytes) is int and 0 < chain_bytes < 1 << 62:
+        return -(-length // chain_bytes)
+    return num_chains(length, chain_bytes)
+
+
+def _raw_stream(s, idx):
+    return _torch._C._cuda_getCurrentRawStream(idx) if s is None else _stream(s)
+
+
+def _call(fn, idx, *args):
+    """fn(*args) with device idx current."""
+    if _torch._C._cuda_getDevice() == idx:
+        _check(fn(*args))
+    else:
+        with _torch.cuda.device(idx):
+            _check(fn(*args))
 
 
 def _aad_bytes(aad, n, what="aad", aad_bytes=None, **kw):
@@ -204,65 +252,56 @@ def decrypt_verify(key, base_iv, chain_bytes, ct, tags, aad=None, out=None, ok=N
     """Decrypt + verify every chain of ct (uint8 CUDA tensor). Returns (pt, ok).
     tags holds n x 16 bytes and aad (optional) n x aad_bytes bytes, n = num_chains."""
     _u8(ct, "ct")
-    dev = ct.device
-    n = num_chains(ct.numel(), chain_bytes)
-    _u8(tags, "tags", numel=16 * n, device=dev)
-    aad_bytes = _aad_bytes(aad, n, device=dev)
+    dev, idx, size = ct.device, ct.get_device(), ct.numel()
+    n = _chains(size, chain_bytes)
+    tags_p = _dev_ptr(tags, "tags", 16 * n, idx, dev)
+    aad_p, aad_bytes = _dev_aad(aad, n, idx, dev)
     new = []
     if out is None:
         out = _torch.empty_like(ct)
         new.append(out)
     if ok is None:
-        ok = _torch.empty(n, dtype=_torch.uint8, device=dev)
+        ok = _torch.empty(n, dtype=_uint8, device=dev)
         new.append(ok)
-    _u8(out, "out", numel=ct.numel(), device=dev)
-    _u8(ok, "ok", numel=n, device=dev)
-    with _torch.cuda.device(dev):
-        _check(lib().fastrack_gcm_decrypt_verify(_host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
-                                                 chain_bytes, _dptr(ct), ct.numel(), _dptr(tags), _dptr(aad),
-                                                 aad_bytes, _dptr(out), _dptr(ok), flags, _stream(stream)))
+    out_p, ok_p = _dev_ptr(out, "out", size, idx, dev), _dev_ptr(ok, "ok", n, idx, dev)
+    _call(lib().fastrack_gcm_decrypt_verify, idx, _host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
+          chain_bytes, ct.data_ptr(), size, tags_p, aad_p, aad_bytes, out_p, ok_p, flags, _raw_stream(stream, idx))
+    if new and stream is not None:
         _used_on(new, [stream], dev)
     return out, ok
-
 
 def decrypt_verify_noalloc(key, base_iv, chain_bytes, ct, tags, aad, out, ok, flags=0, stream=None):
     """decrypt_verify through the allocation-free entry point: the caller passes every
     buffer (out, ok) and the library allocates no device memory. Calls on one GPU
     share the library's fixed device area: order calls made on different streams."""
     _u8(ct, "ct")
-    dev = ct.device
-    n = num_chains(ct.numel(), chain_bytes)
-    _u8(tags, "tags", numel=16 * n, device=dev)
-    aad_bytes = _aad_bytes(aad, n, device=dev)
-    _u8(out, "out", numel=ct.numel(), device=dev)
-    _u8(ok, "ok", numel=n, device=dev)
-    with _torch.cuda.device(dev):
-        _check(lib().fastrack_gcm_decrypt_verify_noalloc(_host_bytes(key, 32, "key"),
-                                                         _host_bytes(base_iv, 12, "base_iv"), chain_bytes, _dptr(ct),
-                                                         ct.numel(), _dptr(tags), _dptr(aad), aad_bytes, _dptr(out),
-                                                         _dptr(ok), flags, _stream(stream)))
+    dev, idx, size = ct.device, ct.get_device(), ct.numel()
+    n = _chains(size, chain_bytes)
+    tags_p = _dev_ptr(tags, "tags", 16 * n, idx, dev)
+    aad_p, aad_bytes = _dev_aad(aad, n, idx, dev)
+    out_p, ok_p = _dev_ptr(out, "out", size, idx, dev), _dev_ptr(ok, "ok", n, idx, dev)
+    _call(lib().fastrack_gcm_decrypt_verify_noalloc, idx, _host_bytes(key, 32, "key"),
+          _host_bytes(base_iv, 12, "base_iv"), chain_bytes, ct.data_ptr(), size, tags_p, aad_p, aad_bytes, out_p, ok_p,
+          flags, _raw_stream(stream, idx))
     return out, ok
-
 
 def encrypt_tag(key, base_iv, chain_bytes, pt, aad=None, out=None, tags=None, flags=0, stream=None):
     """Encrypt every chain of pt (uint8 CUDA tensor) and produce its tag. Returns (ct, tags)."""
     _u8(pt, "pt")
-    dev = pt.device
-    n = num_chains(pt.numel(), chain_bytes)
-    aad_bytes = _aad_bytes(aad, n, device=dev)
+    dev, idx, size = pt.device, pt.get_device(), pt.numel()
+    n = _chains(size, chain_bytes)
+    aad_p, aad_bytes = _dev_aad(aad, n, idx, dev)
     new = []
     if out is None:
         out = _torch.empty_like(pt)
         new.append(out)
     if tags is None:
-        tags = _torch.empty((n, 16), dtype=_torch.uint8, device=dev)
+        tags = _torch.empty((n, 16), dtype=_uint8, device=dev)
         new.append(tags)
-    _u8(out, "out", numel=pt.numel(), device=dev)
-    _u8(tags, "tags", numel=16 * n, device=dev)
-    with _torch.cuda.device(dev):
-        _check(lib().fastrack_gcm_encrypt_tag(_host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
-                                              chain_bytes, _dptr(pt), pt.numel(), _dptr(aad), aad_bytes, _dptr(out),
-                                              _dptr(tags), flags, _stream(stream)))
+    out_p, tags_p = _dev_ptr(out, "out", size, idx, dev), _dev_ptr(tags, "tags", 16 * n, idx, dev)
+    _call(lib().fastrack_gcm_encrypt_tag, idx, _host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
+          chain_bytes, pt.data_ptr(), size, aad_p, aad_bytes, out_p, tags_p, flags, _raw_stream(stream, idx))
+    if new and stream is not None:
         _used_on(new, [stream], dev)
     return out, tags
 
@@ -296,26 +335,25 @@ def decrypt_eager(key, base_iv, chain_bytes, ct, tags, aad=None, out=None, ok=No
                   verify_stream=None):
     """Decrypt on decrypt_stream and check the tags on verify_stream. Returns an Eager."""
     _u8(ct, "ct")
-    dev = ct.device
-    n = num_chains(ct.numel(), chain_bytes)
-    _u8(tags, "tags", numel=16 * n, device=dev)
-    aad_bytes = _aad_bytes(aad, n, device=dev)
+    dev, idx, size = ct.device, ct.get_device(), ct.numel()
+    n = _chains(size, chain_bytes)
+    tags_p = _dev_ptr(tags, "tags", 16 * n, idx, dev)
+    aad_p, aad_bytes = _dev_aad(aad, n, idx, dev)
     new = []
     if out is None:
         out = _torch.empty_like(ct)
         new.append(out)
     if ok is None:
-        ok = _torch.empty(n, dtype=_torch.uint8, device=dev)
+        ok = _torch.empty(n, dtype=_uint8, device=dev)
         new.append(ok)
-    _u8(out, "out", numel=ct.numel(), device=dev)
-    _u8(ok, "ok", numel=n, device=dev)
+    out_p, ok_p = _dev_ptr(out, "out", size, idx, dev), _dev_ptr(ok, "ok", n, idx, dev)
+    vs = verify_stream if verify_stream is not None else decrypt_stream
+    _call(lib().fastrack_gcm_decrypt_eager, idx, _host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
+          chain_bytes, ct.data_ptr(), size, tags_p, aad_p, aad_bytes, out_p, ok_p, _raw_stream(decrypt_stream, idx),
+          _raw_stream(vs, idx))
+    if new and vs is not None:
+        _used_on(new, [decrypt_stream, vs], dev)
     with _torch.cuda.device(dev):
-        ds = decrypt_stream if decrypt_stream is not None else _torch.cuda.current_stream(dev)
-        vs = verify_stream if verify_stream is not None else ds
-        _check(lib().fastrack_gcm_decrypt_eager(_host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
-                                                chain_bytes, _dptr(ct), ct.numel(), _dptr(tags), _dptr(aad),
-                                                aad_bytes, _dptr(out), _dptr(ok), _stream(ds), _stream(vs)))
-        _used_on(new, [ds, vs], dev)
         ev = _torch.cuda.Event()
         ev.record(_stream_obj(vs, dev))
     return Eager(out, ok, ev)
@@ -327,13 +365,14 @@ def keystream(key, base_iv, chain_bytes, length, chain_base=0, out=None, stream=
     new = []
     if out is None:
         device = _torch.device("cuda", _torch.cuda.current_device()) if device is None else _torch.device(device)
-        out = _torch.empty(length, dtype=_torch.uint8, device=device)
+        out = _torch.empty(length, dtype=_uint8, device=device)
         new.append(out)
     _u8(out, "out", min_numel=length)
-    with _torch.cuda.device(out.device):
-        fn = lib().fastrack_gcm_keystream_bitsliced if bitsliced else lib().fastrack_gcm_keystream
-        _check(fn(_host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"), chain_bytes, chain_base, length,
-                  _dptr(out), _stream(stream)))
+    idx = out.get_device()
+    fn = lib().fastrack_gcm_keystream_bitsliced if bitsliced else lib().fastrack_gcm_keystream
+    _call(fn, idx, _host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"), chain_bytes, chain_base, length,
+          out.data_ptr(), _raw_stream(stream, idx))
+    if new and stream is not None:
         _used_on(new, [stream], out.device)
     return out
 
@@ -343,13 +382,13 @@ def apply_verify(key, base_iv, chain_bytes, ct, ks, tags, aad=None, aad_bytes=No
     """pt = ct XOR ks and the tag check of chains chain_base.. of ct. tags, aad and ok
     are the whole message's arrays, indexed by global chain index. Returns (pt, ok)."""
     _u8(ct, "ct")
-    dev = ct.device
-    _u8(ks, "ks", min_numel=ct.numel(), device=dev)
+    dev, idx, size = ct.device, ct.get_device(), ct.numel()
+    _u8(ks, "ks", min_numel=size, device=dev)
     _u8(tags, "tags", device=dev)
     if tags.numel() % 16:
         raise ValueError("tags must hold whole 16-byte tags, got %d bytes" % tags.numel())
     total = tags.numel() // 16
-    n = num_chains(ct.numel(), chain_bytes)
+    n = _chains(size, chain_bytes)
     if chain_base + n > total:
         raise ValueError("tags hold %d chains, need %d" % (total, chain_base + n))
     aad_bytes = _aad_bytes(aad, total, aad_bytes=aad_bytes, device=dev)
@@ -358,14 +397,14 @@ def apply_verify(key, base_iv, chain_bytes, ct, ks, tags, aad=None, aad_bytes=No
         out = _torch.empty_like(ct)
         new.append(out)
     if ok is None:
-        ok = _torch.empty(total, dtype=_torch.uint8, device=dev)
+        ok = _torch.empty(total, dtype=_uint8, device=dev)
         new.append(ok)
-    _u8(out, "out", numel=ct.numel(), device=dev)
+    out_p = _dev_ptr(out, "out", size, idx, dev)
     _u8(ok, "ok", min_numel=chain_base + n, device=dev)
-    with _torch.cuda.device(dev):
-        _check(lib().fastrack_gcm_apply_verify(_host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
-                                               chain_bytes, chain_base, _dptr(ct), ct.numel(), _dptr(ks), _dptr(tags),
-                                               _dptr(aad), aad_bytes, _dptr(out), _dptr(ok), _stream(stream)))
+    _call(lib().fastrack_gcm_apply_verify, idx, _host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
+          chain_bytes, chain_base, ct.data_ptr(), size, ks.data_ptr(), tags.data_ptr(), _dptr(aad), aad_bytes, out_p,
+          ok.data_ptr(), _raw_stream(stream, idx))
+    if new and stream is not None:
         _used_on(new, [stream], dev)
     return out, ok
 
@@ -480,25 +519,23 @@ def decrypt_verify_ragged(key, base_iv, chain_off, chain_len, ct, tags, aad=None
     """Decrypt + verify chains of their own offsets and lengths in ct (uint8 CUDA tensor). Returns (pt, ok);
     bytes of pt outside every chain are left as they were."""
     _u8(ct, "ct")
-    dev = ct.device
-    off, ln = _ragged_layout(chain_off, chain_len, ct.numel(), "ct")
+    dev, idx, size = ct.device, ct.get_device(), ct.numel()
+    off, ln = _ragged_layout(chain_off, chain_len, size, "ct")
     n = off.size
-    _u8(tags, "tags", numel=16 * n, device=dev)
-    aad_bytes = _aad_bytes(aad, n, device=dev)
+    tags_p = _dev_ptr(tags, "tags", 16 * n, idx, dev)
+    aad_p, aad_bytes = _dev_aad(aad, n, idx, dev)
     new = []
     if out is None:
         out = _torch.empty_like(ct)
         new.append(out)
     if ok is None:
-        ok = _torch.empty(n, dtype=_torch.uint8, device=dev)
+        ok = _torch.empty(n, dtype=_uint8, device=dev)
         new.append(ok)
-    _u8(out, "out", numel=ct.numel(), device=dev)
-    _u8(ok, "ok", numel=n, device=dev)
-    with _torch.cuda.device(dev):
-        _check(lib().fastrack_gcm_decrypt_verify_ragged(_host_bytes(key, 32, "key"),
-                                                        _host_bytes(base_iv, 12, "base_iv"), off.ctypes.data,
-                                                        ln.ctypes.data, n, _dptr(ct), _dptr(tags), _dptr(aad),
-                                                        aad_bytes, _dptr(out), _dptr(ok), _stream(stream)))
+    out_p, ok_p = _dev_ptr(out, "out", size, idx, dev), _dev_ptr(ok, "ok", n, idx, dev)
+    _call(lib().fastrack_gcm_decrypt_verify_ragged, idx, _host_bytes(key, 32, "key"),
+          _host_bytes(base_iv, 12, "base_iv"), off.ctypes.data, ln.ctypes.data, n, ct.data_ptr(), tags_p, aad_p,
+          aad_bytes, out_p, ok_p, _raw_stream(stream, idx))
+    if new and stream is not None:
         _used_on(new, [stream], dev)
     return out, ok
 
@@ -506,23 +543,21 @@ def decrypt_verify_ragged(key, base_iv, chain_off, chain_len, ct, tags, aad=None
 def encrypt_tag_ragged(key, base_iv, chain_off, chain_len, pt, aad=None, out=None, tags=None, stream=None):
     """Encrypt + tag chains of their own offsets and lengths in pt (uint8 CUDA tensor). Returns (ct, tags)."""
     _u8(pt, "pt")
-    dev = pt.device
-    off, ln = _ragged_layout(chain_off, chain_len, pt.numel(), "pt")
+    dev, idx, size = pt.device, pt.get_device(), pt.numel()
+    off, ln = _ragged_layout(chain_off, chain_len, size, "pt")
     n = off.size
-    aad_bytes = _aad_bytes(aad, n, device=dev)
+    aad_p, aad_bytes = _dev_aad(aad, n, idx, dev)
     new = []
     if out is None:
         out = _torch.empty_like(pt)
         new.append(out)
     if tags is None:
-        tags = _torch.empty((n, 16), dtype=_torch.uint8, device=dev)
+        tags = _torch.empty((n, 16), dtype=_uint8, device=dev)
         new.append(tags)
-    _u8(out, "out", numel=pt.numel(), device=dev)
-    _u8(tags, "tags", numel=16 * n, device=dev)
-    with _torch.cuda.device(dev):
-        _check(lib().fastrack_gcm_encrypt_tag_ragged(_host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
-                                                     off.ctypes.data, ln.ctypes.data, n, _dptr(pt), _dptr(aad),
-                                                     aad_bytes, _dptr(out), _dptr(tags), _stream(stream)))
+    out_p, tags_p = _dev_ptr(out, "out", size, idx, dev), _dev_ptr(tags, "tags", 16 * n, idx, dev)
+    _call(lib().fastrack_gcm_encrypt_tag_ragged, idx, _host_bytes(key, 32, "key"), _host_bytes(base_iv, 12, "base_iv"),
+          off.ctypes.data, ln.ctypes.data, n, pt.data_ptr(), aad_p, aad_bytes, out_p, tags_p, _raw_stream(stream, idx))
+    if new and stream is not None:
         _used_on(new, [stream], dev)
     return out, tags
 
