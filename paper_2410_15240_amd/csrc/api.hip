@@ -44,6 +44,7 @@ constexpr size_t kMaxKeys = 8;
 constexpr int kMinSmallSegLog2 = 7;                     // small launches: down to 128 blocks (2 per lane)
 constexpr uint64_t kMaxSmallSegs = 512;                 // ... with at most this many segments per chain
 constexpr int kMaxPipelineDepth = 8;                    // staging-ring slots
+constexpr size_t kSmallTables = 64 << 10;               // ragged tables uploaded on the caller's stream up to this size
 constexpr uint64_t kD2hGroupBytes = 32ull << 20;        // D2H: encrypted bytes per copy-stream wait
 
 struct KeyEntry {
@@ -69,26 +70,31 @@ struct KeyPool {
     bool used[kMaxKeys] = {};
 };
 
+// Ragged calls the calling thread may run ahead of the device before it waits for the
+// tables of an earlier one to be read. With two, back-to-back small calls met that wait
+// every time (8 samples of 16 chains: 42 us a call, 34 with a slower caller).
+constexpr int kRaggedRing = 4;
+
 struct ScratchEntry {
     int dev;
     hipStream_t stream;
     void *ptr;
     size_t bytes;
-    // two pinned host staging buffers for the tables of ragged launches, used in
-    // turn, and for each the event after the copy that last read it
-    void *host[2] = {nullptr, nullptr};
-    void *host_dev[2] = {nullptr, nullptr};   // their device addresses
-    size_t host_bytes[2] = {0, 0};
-    hipEvent_t host_read[2] = {nullptr, nullptr};
+    // pinned host staging buffers for the tables of ragged launches, used in turn,
+    // and for each the event after the upload that last read it
+    void *host[kRaggedRing] = {};
+    void *host_dev[kRaggedRing] = {};   // their device addresses
+    size_t host_bytes[kRaggedRing] = {};
+    hipEvent_t host_read[kRaggedRing] = {};
     int cur = 0;
-    // Ragged launches: two device table slots (written only by the uploads, read
-    // only by the ragged kernels), the library's upload stream, and for each slot
-    // the event after the kernels that last read it.
+    // Ragged launches: device table slots (written only by the uploads, read only by
+    // the ragged kernels), the library's upload stream, and for each slot the event
+    // after the kernels that last read it.
     void *rtab = nullptr;
     size_t rtab_slot = 0;
     hipStream_t up = nullptr;
-    hipEvent_t slot_free[2] = {nullptr, nullptr};
-    bool slot_used[2] = {false, false};
+    hipEvent_t slot_free[kRaggedRing] = {};
+    bool slot_used[kRaggedRing] = {};
 };
 
 struct DevInfo {
@@ -265,8 +271,8 @@ int scratch_for(int dev, hipStream_t s, size_t bytes, void **out)
 }
 
 // Pinned host staging of at least `bytes` for (device, stream), free to overwrite:
-// the copy that last read it has completed. Two buffers are used in turn, so the
-// tables of the next call are written while the copy of the last one is pending.
+// the upload that last read it has completed. The buffers are used in turn, so the
+// tables of the next calls are written while earlier uploads are pending.
 int staging_for(int dev, hipStream_t s, size_t bytes, uint8_t **out)
 {
     ScratchEntry *e = nullptr;
@@ -277,11 +283,14 @@ int staging_for(int dev, hipStream_t s, size_t bytes, uint8_t **out)
         g_scratch.push_back(ScratchEntry{dev, s, nullptr, 0});
         e = &g_scratch.back();
     }
-    e->cur ^= 1;
+    e->cur = (e->cur + 1) % kRaggedRing;
     const int b = e->cur;
     hipError_t he;
-    if (e->host_read[b] && (he = hipEventSynchronize(e->host_read[b])) != hipSuccess)
-        return hip_fail(he, "hipEventSynchronize");
+    if (e->host_read[b] && hipEventQuery(e->host_read[b]) != hipSuccess) {
+        (void)hipGetLastError();   // not ready is no error
+        if ((he = hipEventSynchronize(e->host_read[b])) != hipSuccess)
+            return hip_fail(he, "hipEventSynchronize");
+    }
     if (!e->host_read[b] && (he = hipEventCreateWithFlags(&e->host_read[b], hipEventDisableTiming)) != hipSuccess) {
         e->host_read[b] = nullptr;
         return hip_fail(he, "hipEventCreate");
@@ -1308,7 +1317,7 @@ int ragged_slot(int dev, hipStream_t s, int b, size_t bytes, ScratchEntry **out_
             e->up = nullptr;
             return hip_fail(he, "hipStreamCreate for the table uploads");
         }
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < kRaggedRing; ++k)
             if ((he = hipEventCreateWithFlags(&e->slot_free[k], hipEventDisableTiming)) != hipSuccess) {
                 e->slot_free[k] = nullptr;
                 return hip_fail(he, "hipEventCreate");
@@ -1321,12 +1330,14 @@ int ragged_slot(int dev, hipStream_t s, int b, size_t bytes, ScratchEntry **out_
             (void)hipFree(e->rtab);
             e->rtab = nullptr;
             e->rtab_slot = 0;
-            e->slot_used[0] = e->slot_used[1] = false;
+            for (bool &u : e->slot_used)
+                u = false;
         }
         const size_t slot = (bytes + (1u << 20) - 1) & ~(size_t)((1u << 20) - 1);   // whole MiB, fewer regrowths
-        if ((he = hipMalloc(&e->rtab, 2 * slot)) != hipSuccess) {
+        if ((he = hipMalloc(&e->rtab, kRaggedRing * slot)) != hipSuccess) {
             e->rtab = nullptr;
-            return fail(FASTRACK_ENOMEM, "hipMalloc(%zu) for the ragged tables: %s", 2 * slot, hipGetErrorString(he));
+            return fail(FASTRACK_ENOMEM, "hipMalloc(%zu) for the ragged tables: %s", kRaggedRing * slot,
+                        hipGetErrorString(he));
         }
         e->rtab_slot = slot;
     }
@@ -1468,11 +1479,12 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
         return rc;
     RaggedChain *hc = reinterpret_cast<RaggedChain *>(host);
     uint32_t *hi = reinterpret_cast<uint32_t *>(host + round256(n * sizeof(RaggedChain)));
-    // Item order: every chain's segment 0 (the short one, or the whole chain) first,
-    // longest first, then the full-length segments chain by chain. A wave-item runs
-    // as many iterations as its longest item, so items of like length side by side
-    // waste fewer lanes (on the 1024-sample batch: 98.5% of the lane-iterations
-    // useful instead of 89%).
+    // Item order: the full-length segments chain by chain, then every chain's segment 0
+    // (the short one, or the whole chain), longest first: the last pass of wave-items has
+    // the shortest. A wave-item runs as many iterations as its longest item, so items of
+    // like length side by side waste fewer lanes (on the 1024-sample batch: 98.5% of the
+    // lane-iterations useful instead of 89%).
+    const uint64_t n_full = n_items - n;
     it0.resize(n);   // iterations of each chain's segment 0, then its item number
     uint32_t max_it0 = 0;
     const uint32_t lmask = (1u << lg) - 1, lstep = (1u << ll) - 1;
@@ -1493,7 +1505,7 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
             run += k;
         }
         for (uint64_t i = 0; i < n; ++i) {
-            const uint32_t k = cnt[max_it0 - it0[i]]++;
+            const uint32_t k = (uint32_t)n_full + cnt[max_it0 - it0[i]]++;
             it0[i] = k;
             hi[k] = (uint32_t)i;
         }
@@ -1503,13 +1515,12 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
             order[i] = (uint32_t)i;
         std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return it0[a] > it0[b]; });
         for (uint64_t k = 0; k < n; ++k) {
-            it0[order[k]] = (uint32_t)k;
-            hi[k] = order[k];
+            it0[order[k]] = (uint32_t)(n_full + k);
+            hi[n_full + k] = order[k];
         }
     }
-    // The chain table in chain order, one sequential pass (with the full-length
-    // segments' items behind the segment-0 items).
-    uint64_t item = n;
+    // The chain table in chain order, one sequential pass.
+    uint64_t item = 0;
     for (uint64_t i = 0; i < n; ++i) {
         const uint32_t sg = segs_of(q[i], lg);
         RaggedChain &c = hc[i];
@@ -1524,18 +1535,22 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     // A copy kernel reads the pinned tables over the host link: hipMemcpyAsync held
     // the calling thread until the stream reached the copy, leaving the GPU idle
     // while the host then prepared the launch.
-    // The upload runs on the library's upload stream, so it overlaps the kernels of
-    // the call before: it waits only for the kernels that last read this slot (two
-    // calls back), and the kernels of this call wait for it.
+    // The upload of large tables runs on the library's upload stream, so it overlaps
+    // the kernels of the call before: it waits only for the kernels that last read this
+    // slot (kRaggedRing calls back), and the kernels of this call wait for it. Small
+    // tables go up on the caller's stream: their upload takes 2 us, less than the two
+    // streams' waits for each other.
     hipError_t he;
     const void *host_dev = se->host_dev[slot];   // the staging buffer's device address
-    if (se->slot_used[slot] && (he = hipStreamWaitEvent(se->up, se->slot_free[slot], 0)) != hipSuccess)
+    const bool own = tab_bytes > kSmallTables;
+    hipStream_t us = own ? se->up : s;
+    if (own && se->slot_used[slot] && (he = hipStreamWaitEvent(us, se->slot_free[slot], 0)) != hipSuccess)
         return hip_fail(he, "hipStreamWaitEvent");
-    if ((he = launch_upload(host_dev, tab, tab_bytes, se->up)) != hipSuccess)
+    if ((he = launch_upload(host_dev, tab, tab_bytes, us)) != hipSuccess)
         return hip_fail(he, "chain table upload");
-    if ((rc = staging_read(dev, s, se->up)))   // the staging is read once the upload has run
+    if ((rc = staging_read(dev, s, us)))   // the staging is read once the upload has run
         return rc;
-    if ((he = hipStreamWaitEvent(s, se->host_read[slot], 0)) != hipSuccess)
+    if (own && (he = hipStreamWaitEvent(s, se->host_read[slot], 0)) != hipSuccess)
         return hip_fail(he, "hipStreamWaitEvent");
 
     GcmLaunch p;
@@ -1657,7 +1672,7 @@ FT_EXPORT void fastrack_shutdown(void)
     for (auto &s : g_scratch) {
         (void)hipFree(s.ptr);
         (void)hipFree(s.rtab);
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < kRaggedRing; ++b) {
             if (s.host[b])
                 (void)hipHostFree(s.host[b]);
             if (s.host_read[b])

@@ -38,8 +38,8 @@ constexpr int gcm_wgs_per_cu(int mode)
 
 // One chain of a ragged launch: bytes [off, off + len) of the buffers (off a
 // multiple of 16), cut into `segs` segments. Items (and their partial slots) are
-// ordered with every chain's segment 0 first, then the other segments chain by
-// chain: segment 0 is item item0, segment s >= 1 is item item_base + s.
+// ordered with the full-length segments first, chain by chain, then every chain's
+// segment 0: segment 0 is item item0, segment s >= 1 is item item_base + s.
 struct RaggedChain {
     uint64_t off;
     uint64_t len;
