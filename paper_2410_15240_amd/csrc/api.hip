@@ -408,10 +408,15 @@ void make_plan(uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t
         while (lg > (uint32_t)kMinSmallSegLog2 && items_at(lg) < slots / 2 &&
                ((qc + (1ull << (lg - 1)) - 1) >> (lg - 1)) <= kMaxSmallSegs)
             --lg;
+    // The smallest, with at most one 64-block item per CU: one iteration each (an image of
+    // 150,528 bytes in 16 chains).
+    if (ll == 6 && lg == (uint32_t)kMinSmallSegLog2 && items_at(6) <= slots / kGcmWavesPerWg)
+        lg = 6;
     p.lanes_log2 = ll;
     p.seg_log2 = lg;
     p.segs_full = (uint32_t)((qc + (1ull << lg) - 1) >> lg);
     p.segs_last = (uint32_t)((p.q_last + (1ull << lg) - 1) >> lg);
+    p.segs_recip = p.segs_full > 1 ? (uint32_t)((1ull << 32) / p.segs_full) : 0xFFFFFFFFu;
     p.n_items = (n - 1) * p.segs_full + p.segs_last;
 }
 

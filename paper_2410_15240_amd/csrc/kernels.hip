@@ -291,8 +291,14 @@ __device__ __forceinline__ ItemPos item_pos(const GcmLaunch &p, uint64_t item)
         r.tail = (uint32_t)(rc.len & 15);
     } else {
         const uint32_t it32 = (uint32_t)item;   // the host keeps a launch's items below 2^32
-        r.chain = it32 / p.segs_full;
+        // it32 / segs_full with floor(2^32 / segs_full) (2^32 - 1 for 1): at most 2 too small
+        r.chain = __umulhi(it32, p.segs_recip);
         r.s = it32 - r.chain * p.segs_full;
+        for (int fix = 0; fix < 2; ++fix) {
+            const uint32_t up = r.s >= p.segs_full ? 1u : 0u;
+            r.chain += up;
+            r.s -= up ? p.segs_full : 0u;
+        }
         const bool last = r.chain == p.n_chains - 1;
         r.q = last ? p.q_last : p.qc;
         r.S = last ? p.segs_last : p.segs_full;
@@ -821,14 +827,14 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     for (int i = 0; i < 60; ++i)
         rk[i] = kAes ? c->rk16[i] : 0u;
 
-    const uint64_t nwaves = (uint64_t)gridDim.x * kWavesPerWg;
+    const uint32_t nwaves = gridDim.x * kWavesPerWg;
     // Unless every wave takes the same number of wave-items, waves are numbered across
     // the workgroups first, which spreads a launch's only or last, partial pass of
     // wave-items over all CUs; otherwise each workgroup's waves keep consecutive wave-items.
-    const bool spread = ((p.n_items + G - 1) / G) % nwaves != 0;
+    const bool spread = p.last_pass != 0;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(spread ? (tid >> 6) * gridDim.x + blockIdx.x
                                                                 : blockIdx.x * kWavesPerWg + (tid >> 6));
-    const uint64_t n_wave_items = (p.n_items + G - 1) / G;
+    const uint32_t n_wave_items = p.wave_items;
     const uint32_t seg = 1u << p.seg_log2;
     const uint32_t Ku_uniform = ((seg < p.qc ? seg : p.qc) + L - 1) >> LL;   // iterations per item
     // The tag mask AES_K(J0) xor L . H of the chains of this wave's next L
@@ -906,7 +912,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     // per chain, its position fixed by the chain index alone).
     const bool idle_masks = kGhash && SPLIT && p.idle_masks != 0;
     if (idle_masks && wave >= n_wave_items) {
-        const uint64_t c0 = ((uint64_t)wave - n_wave_items) * 64;   // uniform
+        const uint64_t c0 = (uint64_t)(wave - n_wave_items) * 64;   // uniform
         if (c0 < p.n_chains) {
             const uint64_t c = c0 + lane;
             uint64_t bitem = p.n_items;   // no chain: nothing needed
@@ -1449,6 +1455,8 @@ static hipError_t launch_mode(const GcmLaunch &p, int num_cu, hipStream_t s)
     // One item per wave with every chain's segments inside one workgroup: the
     // workgroup tags the chains itself and the per-chain tag kernel is not needed.
     GcmLaunch q = p;
+    q.wave_items = (uint32_t)waves;
+    q.last_pass = (uint32_t)(waves % (wgs * kWavesPerWg));
     q.wg_tag = MODE == kFused && !RAG && split && p.lanes_log2 == 6 && p.n_items == wgs * kWavesPerWg &&
                p.segs_full <= (uint32_t)kWavesPerWg && kWavesPerWg % p.segs_full == 0;
     q.idle_masks = split && !q.wg_tag && wgs * kWavesPerWg >= waves + (p.n_chains + 63) / 64;

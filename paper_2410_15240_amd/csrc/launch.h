@@ -69,6 +69,10 @@ struct GcmLaunch {
     uint32_t lanes_log2;        // lanes per item: 4 (16), 5 (32) or 6 (64); the Horner stride
     uint32_t segs_full;         // segments of a full chain
     uint32_t segs_last;         // segments of the last chain
+    uint32_t segs_recip;        // floor(2^32 / segs_full), 2^32 - 1 for 1
+    // Set by the launch: the wave-items (64 >> lanes_log2 items each) and how many waves of
+    // the grid take one more of them than the others.
+    uint32_t wave_items, last_pass;
     uint32_t iv[3];             // base IV as little-endian words
     uint32_t aad_bytes;
     const uint8_t *aad;         // global chain i's AAD at aad + i * aad_bytes
