@@ -643,6 +643,10 @@ __device__ inline void emit_tag(const GcmLaunch &p, uint64_t gchain, const u4 &t
     }
 }
 
+// s_waitcnt for all vector memory accesses and nothing else (gfx9 encoding: vmcnt in bits
+// 3:0 and 15:14, expcnt in 6:4, lgkmcnt in 11:8).
+constexpr int kWaitVm0 = 0x0F70;
+
 // Compile-time switches for the streaming kernel's iteration step: whether the
 // iteration may hold AAD blocks.
 struct AadSteps {
@@ -951,19 +955,6 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
         }
         uint32_t iv[3];
         chain_iv(p, gchain, iv);
-        // Counter mode: columns 0..2 of the state after AddRoundKey are the IV and
-        // fixed for the whole chain, so 12 of round 1's 16 lookups are too.
-        uint32_t p0 = 0, p1 = 0, p2 = 0, p3 = 0;
-        if constexpr (kAes) {
-            // (rk[4..7] are rotated by 16 bits; T2 = rotl16(T0), T3 = rotl16(T1).)
-            const uint32_t c0 = iv[0] ^ rk[0], c1 = iv[1] ^ rk[1], c2 = iv[2] ^ rk[2];
-            p0 = xor3(tlk(lds, c0, lc0, FT_SEL(0)), tlk(lds, c1, lc1, FT_SEL(1)),
-                      rotl16(tlk(lds, c2, lc0, FT_SEL(2)) ^ rk[4]));
-            p1 = xor3(tlk(lds, c1, lc0, FT_SEL(0)), tlk(lds, c2, lc1, FT_SEL(1)),
-                      rotl16(tlk(lds, c0, lc1, FT_SEL(3)) ^ rk[5]));
-            p2 = tlk(lds, c2, lc0, FT_SEL(0)) ^ rotl16(xor3(tlk(lds, c0, lc0, FT_SEL(2)), tlk(lds, c1, lc1, FT_SEL(3)), rk[6]));
-            p3 = tlk(lds, c0, lc1, FT_SEL(1)) ^ rotl16(xor3(tlk(lds, c1, lc0, FT_SEL(2)), tlk(lds, c2, lc1, FT_SEL(3)), rk[7]));
-        }
         const uint8_t *src = kRead ? p.in + ip.off : nullptr;
         uint8_t *dst = kWrite ? p.out + ip.off : nullptr;
         const uint8_t *ksrc = MODE == kApplyKs ? p.ks + ip.off : nullptr;
@@ -999,6 +990,20 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
                 const u4 g = v >= -na ? aad_block(aad_c, (uint32_t)(v + na), p.aad_bytes) : zero4();
                 acc = k == kmin ? g : ghash_step(lds, acc, g, gk);
             }
+        }
+        // (After the loads of the received tag and the AAD, which arrive meanwhile.)
+        // Counter mode: columns 0..2 of the state after AddRoundKey are the IV and
+        // fixed for the whole chain, so 12 of round 1's 16 lookups are too.
+        uint32_t p0 = 0, p1 = 0, p2 = 0, p3 = 0;
+        if constexpr (kAes) {
+            // (rk[4..7] are rotated by 16 bits; T2 = rotl16(T0), T3 = rotl16(T1).)
+            const uint32_t c0 = iv[0] ^ rk[0], c1 = iv[1] ^ rk[1], c2 = iv[2] ^ rk[2];
+            p0 = xor3(tlk(lds, c0, lc0, FT_SEL(0)), tlk(lds, c1, lc1, FT_SEL(1)),
+                      rotl16(tlk(lds, c2, lc0, FT_SEL(2)) ^ rk[4]));
+            p1 = xor3(tlk(lds, c1, lc0, FT_SEL(0)), tlk(lds, c2, lc1, FT_SEL(1)),
+                      rotl16(tlk(lds, c0, lc1, FT_SEL(3)) ^ rk[5]));
+            p2 = tlk(lds, c2, lc0, FT_SEL(0)) ^ rotl16(xor3(tlk(lds, c0, lc0, FT_SEL(2)), tlk(lds, c1, lc1, FT_SEL(3)), rk[6]));
+            p3 = tlk(lds, c0, lc1, FT_SEL(1)) ^ rotl16(xor3(tlk(lds, c1, lc0, FT_SEL(2)), tlk(lds, c2, lc1, FT_SEL(3)), rk[7]));
         }
         // The lane's slot in iteration k: v = k L + jl - pad (below 0: a padding slot),
         // block t of the chain; a final partial block holds `tail` bytes.
@@ -1116,12 +1121,16 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
                 acc = (k == 0 && kmin == 0) ? g : ghash_step(lds, acc, g, gk);
             }
         };
-        auto pace = [&](uint32_t k) {
-            const uint32_t mine = iters_done + k;
+        // Publish this wave's progress and read the SIMD's; then, once the read has arrived
+        // (in the AES iterations at their end, so that nothing waits for it), take the priority.
+        auto pace_read = [&](uint32_t k) {
             if (lane == 0)
-                prog[pidx] = mine;
+                prog[pidx] = iters_done + k;
             asm volatile("" ::: "memory");   // the store is made, the others' counters re-read
-            const v4u g = *(const lds_v4u *)(reinterpret_cast<uint32_t *>(lds4) + kProg + (pidx & ~3u));
+            return *(const lds_v4u *)(reinterpret_cast<uint32_t *>(lds4) + kProg + (pidx & ~3u));
+        };
+        auto pace_set = [&](uint32_t k, const v4u &g) {
+            const uint32_t mine = iters_done + k;
             const uint32_t mn = __builtin_amdgcn_readfirstlane(min(min(g.x, g.y), min(g.z, g.w)));
             const uint32_t lead = mine - (mn < mine ? mn : mine);
             if (lead == 0u)
@@ -1133,6 +1142,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
             else
                 __builtin_amdgcn_s_setprio(0);
         };
+        auto pace = [&](uint32_t k) { pace_set(k, pace_read(k)); };
         if constexpr (!kAes && kRead && !(SPLIT && LL < 6)) {
             // No AES between a load and its use to hide the memory latency: the loads
             // run up to four iterations ahead of the GHASH steps, in a queue of
@@ -1226,6 +1236,10 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
             for (uint32_t k = 0; k < Ku;) {
                 if (kAes && k >= k_a && k < k_b) {
                     uint32_t t = ip.b + (uint32_t)((int)(k << LL) + (int)jl - pad);
+                    // The received tag and the AAD have had the set-up above to arrive. With a
+                    // load of theirs or of an iteration before pending here, every iteration
+                    // would start with a wait for the store of the one before it.
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);
                     do {
                         pace(k);
                         v4u dv = {0u, 0u, 0u, 0u};
