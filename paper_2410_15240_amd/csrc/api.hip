@@ -335,14 +335,36 @@ uint32_t ceil_log2(uint64_t x)
     return r;
 }
 
+// What a wave-item costs in a mode, in iterations of a wave when all its CU's waves are
+// busy. With a share w of them at work an iteration takes 1 - slope (1 - w) of that, as the
+// waves share the LDS, but no less than `floor` (its dependent lookups); every wave-item
+// adds `item` for its set-up and tail. Measured: decrypt + verify 3.6 us an iteration, 2.5 at
+// 8 of 16 waves, 2.1 at the least, and about 4 us an item; the checks without AES 0.66 us,
+// 0.56 at 8 waves, 0.48 at the least, and 3 us an item; keystream-apply 1.4 us an iteration,
+// held up by the memory; the AES-only modes have no tail.
+struct PlanCost {
+    double floor, slope, item;
+};
+
+PlanCost plan_cost_of(GcmMode mode)
+{
+    switch (mode) {
+    case kCtr:
+    case kKeystream:
+        return {0.58, 0.6, 0.4};
+    case kVerify:
+        return {0.73, 0.3, 4.5};
+    case kApplyKs:
+        return {0.73, 0.3, 2.5};
+    default:
+        return {0.58, 0.6, 1.0};
+    }
+}
+
 // Estimated time of a uniform launch of n chains of qc blocks (the last of q_last), 2^ll
-// lanes per item and segments of 2^lg blocks, in iterations of a wave when all its CU's
-// waves are busy (3.6 us for decrypt + verify). With a share w of a CU's waves at work an
-// iteration takes 0.4 + 0.6 w of that (2.5 us at 8 of 16), as the waves share the LDS, but no
-// less than 0.58 (its dependent lookups, 2.1 us). Every wave-item adds its set-up and tail,
-// about one iteration. `slots` wave-items run at once; a last, partial pass is spread over
-// the CUs.
-double plan_cost(uint64_t n, uint64_t qc, uint64_t q_last, uint32_t ll, uint32_t lg, uint64_t slots)
+// lanes per item and segments of 2^lg blocks, in such iterations. `slots` wave-items run at
+// once; a last, partial pass is spread over the CUs.
+double plan_cost(const PlanCost &pc, uint64_t n, uint64_t qc, uint64_t q_last, uint32_t ll, uint32_t lg, uint64_t slots)
 {
     const uint64_t seg = 1ull << lg, L = 1ull << ll, g = 64u >> ll;
     const uint64_t segs = (qc + seg - 1) >> lg;
@@ -352,10 +374,10 @@ double plan_cost(uint64_t n, uint64_t qc, uint64_t q_last, uint32_t ll, uint32_t
     const double mean = (double)((segs - 1) * it + it0) / (double)segs;
     const uint64_t full = items / slots, rest = items % slots;
     const uint64_t cus = slots / kGcmWavesPerWg ? slots / kGcmWavesPerWg : 1;
-    double t = (double)full * (mean + 1.0);
+    double t = (double)full * (mean + pc.item);
     if (rest) {
-        const double w = 0.4 + 0.6 * (double)((rest + cus - 1) / cus) / kGcmWavesPerWg;
-        t += (double)it * (w > 0.58 ? w : 0.58) + 1.0;
+        const double w = 1.0 - pc.slope * (1.0 - (double)((rest + cus - 1) / cus) / kGcmWavesPerWg);
+        t += (double)it * (w > pc.floor ? w : pc.floor) + pc.item;
     }
     return t;
 }
@@ -367,7 +389,7 @@ double plan_cost(uint64_t n, uint64_t qc, uint64_t q_last, uint32_t ll, uint32_t
 // and segments of few blocks give every wave work when the chains are few; and
 // wave-items that do not divide evenly over the waves leave a last pass in which
 // most of them idle.
-void make_plan(uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t slots, GcmLaunch &p)
+void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t slots, GcmLaunch &p)
 {
     const uint64_t n = (len + chain_bytes - 1) / chain_bytes;
     const uint64_t qc = chain_bytes / 16;
@@ -384,11 +406,12 @@ void make_plan(uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t
     // Segments have at least 4 iterations. For each number of lanes the candidates run
     // from whole chains to the first segment length with 8 wave-items per wave (shorter
     // ones only add tails).
+    const PlanCost pc = plan_cost_of(mode);
     uint32_t ll = 6, lg = lg0;
     double best = -1;
     for (uint32_t l = 6; l >= 4; --l)
         for (uint32_t g = lg0;; --g) {
-            const double c = plan_cost(n, qc, p.q_last, l, g, slots);
+            const double c = plan_cost(pc, n, qc, p.q_last, l, g, slots);
             if (best < 0 || c < best) {
                 best = c;
                 ll = l;
@@ -471,7 +494,7 @@ int run_gcm(bool encrypt, GcmMode mode, const KeyCtx *ctx, const uint8_t *base_i
 {
     GcmLaunch p;
     std::memset(&p, 0, sizeof p);
-    make_plan(len, chain_bytes, chain_base, (uint64_t)num_cu * kGcmWavesPerWg * gcm_wgs_per_cu(mode), p);
+    make_plan(mode, len, chain_bytes, chain_base, (uint64_t)num_cu * kGcmWavesPerWg * gcm_wgs_per_cu(mode), p);
     if (p.n_items > 0xFFFFFFFFull)   // the kernel indexes a launch's items in 32 bits
         return fail(FASTRACK_EINVAL, "more than 2^32-1 work items in one launch");
     p.ctx = ctx;
@@ -554,7 +577,7 @@ FT_EXPORT int fastrack_plan(uint64_t len, uint64_t chain_bytes, uint32_t num_cu,
         return fail(FASTRACK_EINVAL, "len must be nonzero, with at most 2^32-1 chains");
     GcmLaunch p;
     std::memset(&p, 0, sizeof p);
-    make_plan(len, chain_bytes, 0, (uint64_t)num_cu * kGcmWavesPerWg * gcm_wgs_per_cu(kFused), p);
+    make_plan(kFused, len, chain_bytes, 0, (uint64_t)num_cu * kGcmWavesPerWg * gcm_wgs_per_cu(kFused), p);
     const uint64_t L = 1ull << p.lanes_log2, seg = 1ull << p.seg_log2;
     out[0] = p.lanes_log2;
     out[1] = p.seg_log2;
@@ -658,7 +681,7 @@ FT_EXPORT int fastrack_gcm_decrypt_verify_noalloc(const uint8_t *key, const uint
     // Size check before anything is enqueued: the same plan run_gcm makes.
     GcmLaunch probe;
     std::memset(&probe, 0, sizeof probe);
-    make_plan(len, chain_bytes, 0, (uint64_t)ncu * kGcmWavesPerWg * gcm_wgs_per_cu(kFused), probe);
+    make_plan(kFused, len, chain_bytes, 0, (uint64_t)ncu * kGcmWavesPerWg * gcm_wgs_per_cu(kFused), probe);
     if (probe.n_items > 0xFFFFFFFFull)
         return fail(FASTRACK_EINVAL, "more than 2^32-1 work items in one launch");
     const bool seq = (flags & FASTRACK_F_SEQ_GHASH) != 0;
@@ -794,7 +817,7 @@ FT_EXPORT int fastrack_gcm_keystream_bitsliced(const uint8_t *key, const uint8_t
         return rc;
     GcmLaunch p;
     std::memset(&p, 0, sizeof p);
-    make_plan(len, chain_bytes, chain_base, (uint64_t)ncu * kGcmWavesPerWg, p);
+    make_plan(kKeystream, len, chain_bytes, chain_base, (uint64_t)ncu * kGcmWavesPerWg, p);
     p.ctx = ctx;
     p.out = d_ks;
     iv_words(base_iv, p.iv);

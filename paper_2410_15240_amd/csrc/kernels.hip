@@ -357,11 +357,12 @@ static_assert(kTBase * 16 == 0x10000, "one address byte places the T tables");
 constexpr uint32_t kT0GhashOnly = 4096;         // uint4 index: 64 KiB
 constexpr uint32_t kTreeBaseGhashOnly = 4160;   // 65 KiB
 constexpr uint32_t kLdsGhashOnly = (65 + 8 * kTreeLds) * 1024 + 64;
-// Per-wave progress counters (16 words): the last 64 B of either layout.
-constexpr uint32_t kProgBase = kLdsBytes / 4 - 16;
-constexpr uint32_t kProgBaseGhashOnly = kLdsGhashOnly / 4 - 16;
-
-
+// Modes without GHASH: T0 | T1 alone. A workgroup of theirs and one of a GHASH-only mode
+// fit a CU together (64 + 89 KiB, 2048 threads, 48 + 80 VGPRs a lane), so the two kernels of
+// an eager call overlap: one reads the LDS while the other's waves wait.
+constexpr uint32_t kLdsAesOnly = 64 * 1024 + 64;
+static_assert(kLdsAesOnly + kLdsGhashOnly <= 160 * 1024, "an AES-only and a GHASH-only workgroup share a CU");
+// Per-wave progress counters (16 words): the last 64 B of each layout.
 
 #define FT_SEL(k) (0x0C020400u + ((uint32_t)(k) << 8))
 
@@ -741,7 +742,7 @@ __device__ __forceinline__ u4 ghash_step(const char *lds, const u4 &acc, const u
 // GcmMode: which of keystream, data XOR and GHASH + tag the launch computes.
 // RAG: chains of their own offsets and lengths from the launch's chain table.
 template <bool ENC, int LL, bool SPLIT, int MODE, bool RAG>
-__global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) void gcm_kernel(GcmLaunch p)
+__device__ __forceinline__ void gcm_body(const GcmLaunch &p)
 {
     constexpr bool kGhash = MODE == kFused || MODE == kVerify || MODE == kApplyKs;   // GHASH + tag
     constexpr bool kAes = MODE == kFused || MODE == kCtr || MODE == kKeystream;      // keystream by AES
@@ -753,14 +754,15 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     // can be used as the ds_read address with no further add. Modes without
     // data AES hold the GHASH table, a plain T0 (for the J0 masks) and the
     // lane-combine tables, 89 KiB.
-    constexpr uint32_t kLdsUse = kAes ? kLdsBytes : kLdsGhashOnly;
+    constexpr uint32_t kLdsUse = !kGhash ? kLdsAesOnly : (kAes ? kLdsBytes : kLdsGhashOnly);
     __shared__ uint4 lds4[kLdsUse / 16];
     const char *lds = reinterpret_cast<const char *>(lds4);
     constexpr uint32_t kGh = kGhBase;                                 // uint4 index of the GHASH table
     uint32_t *t0l = reinterpret_cast<uint32_t *>(lds4 + kT0GhashOnly);   // GHASH-only modes: T0 after the table
     constexpr uint32_t kTree = kAes ? kTreeBase : kTreeBaseGhashOnly;
     const Tab4 *tree = reinterpret_cast<const Tab4 *>(lds4 + kTree);   // tree[t]: 4-bit table of H^(2^t)
-    constexpr uint32_t kProg = kAes ? kProgBase : kProgBaseGhashOnly;
+    constexpr uint32_t kProg = kLdsUse / 4 - 16;                       // word index of the progress counters
+    constexpr uint32_t kT = kGhash ? kTBase : 0u;                      // uint4 index of T0 | T1
     const int tid = threadIdx.x;
     const uint32_t lane = tid & 63;
     const uint32_t jl = lane & (L - 1);      // lane within the item
@@ -772,7 +774,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
             // Pass k of a wave writes the 64 words (w + k W) * 64 + [0, 64) of region
             // (w + k W) / 256, all from one T0 row: lane k fetches that row up front
             // and each pass broadcasts it, so no pass waits on memory.
-            uint32_t *t = reinterpret_cast<uint32_t *>(lds4 + kTBase);
+            uint32_t *t = reinterpret_cast<uint32_t *>(lds4 + kT);
             constexpr uint32_t kPasses = (16384 + kThreads - 1) / kThreads;
             static_assert(kPasses <= 64, "one T0 row per lane and pass");
             const uint32_t w = (uint32_t)tid >> 6;
@@ -816,9 +818,9 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     }
     __syncthreads();
 
-    const uint32_t lb = ((lane & 31) << 2) | (kTBase * 16);
+    const uint32_t lb = ((lane & 31) << 2) | (kT * 16);
     const uint32_t lc0 = lb, lc1 = lb | 0x80u;
-    const uint32_t m1 = byte1_mask();
+    const uint32_t m1 = MODE == kCtr && LL == 6 ? 0xFF00u : byte1_mask();   // (see ctr64_kernel)
     const GhLane gk = ghash_lane(lane);
     // The 60 round-key words are uniform: they stay in scalar registers (the XORs
     // take them as scalar operands), which keeps the kernel within the 128 VGPRs
@@ -1351,6 +1353,20 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
     }
 }
 
+template <bool ENC, int LL, bool SPLIT, int MODE, bool RAG>
+__global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) void gcm_kernel(GcmLaunch p)
+{
+    gcm_body<ENC, LL, SPLIT, MODE, RAG>(p);
+}
+
+// CTR with 64 lanes per item in 48 VGPRs (47 and the one that holds spilled SGPRs; left
+// alone the body takes 49), so that its workgroup
+// shares a CU with one of the verify kernel's.
+__global__ __launch_bounds__(kThreads, kWavesPerWg / 4) __attribute__((amdgpu_num_vgpr(47))) void ctr64_kernel(GcmLaunch p)
+{
+    gcm_body<false, 6, false, kCtr, false>(p);
+}
+
 // Chains cut into segments: T = mask xor the XOR of the chain's weighted
 // partials. One wave per chain: the lanes load the partials side by side and
 // the wave XOR-sums them.
@@ -1482,6 +1498,8 @@ static hipError_t launch_mode(const GcmLaunch &p, int num_cu, hipStream_t s)
         hipLaunchKernelGGL((gcm_kernel<ENC, 5, false, MODE, RAG>), dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
     else if (p.lanes_log2 == 5)
         hipLaunchKernelGGL((gcm_kernel<ENC, 5, ghash, MODE, RAG>), dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
+    else if (MODE == kCtr)
+        hipLaunchKernelGGL(ctr64_kernel, dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
     else if (!split)
         hipLaunchKernelGGL((gcm_kernel<ENC, 6, false, MODE, RAG>), dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
     else
