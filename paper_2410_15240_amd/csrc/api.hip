@@ -1426,21 +1426,15 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     if ((rc = key_ctx(key, s, dev, &ctx)))
         return rc;
 
-    // Plan: lanes per item from the mean chain length, as for uniform chains. Chains
-    // of their own lengths leave the waves unevenly loaded when a wave takes few
-    // items, so chains are cut into segments of one size (2^lg blocks, at least
-    // 4 iterations of the item's lanes) until every wave has about 4 wave-items (fewer
-    // and longer items than that pay their tails too often; more leave waves uneven).
+    // Plan: lanes per item and one segment size for all chains (2^lg blocks, at least 4
+    // iterations of the item's lanes), the pair with the least estimated time. Chains of
+    // their own lengths load the waves unevenly when each takes few items; cut finer, they
+    // pay a set-up and a tail more often. The estimate takes up to 512 of the chains and has
+    // the units of plan_cost: the items' iterations and about one per item for set-up and tail
+    // over the waves, and a last, partial pass of the shortest items. (1024 samples of 16
+    // chains: 16 lanes and 256 blocks, 186 us; 128 blocks 193, 512 188. 256 samples: 32 lanes
+    // and 512 blocks, 63 us; 256 blocks 66, 64 lanes and 256 blocks 72.)
     const uint64_t slots = (uint64_t)ncu * kGcmWavesPerWg;
-    const uint64_t qmean = (blocks + n - 1) / n;
-    uint32_t ll = 0;
-    for (uint32_t cand = 4; cand <= 6; ++cand)
-        if (qmean >= (4ull << cand) && ((n << cand) + 63) / 64 >= slots) {
-            ll = cand;
-            break;
-        }
-    if (ll == 0)
-        ll = qmean >= 256 ? 6 : (qmean >= 128 ? 5 : 4);
     uint32_t lg0 = ceil_log2(qmax > 0 ? qmax : 1);
     if (lg0 > 31)
         lg0 = 31;
@@ -1449,40 +1443,54 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
         const uint32_t sg = (x >> g) + ((x & ((1u << g) - 1)) != 0);
         return sg ? sg : 1u;
     };
+    const PlanCost pc = plan_cost_of(kFused);
+    const uint64_t stride = (n + 511) / 512;
+    auto ragged_cost = [&](uint32_t l, uint32_t g) {
+        const uint32_t step = (1u << l) - 1, mask = (1u << g) - 1;
+        uint64_t full = 0, rest_it = 0, taken = 0;   // full segments; iterations of the segments 0
+        for (uint64_t i = 0; i < n; i += stride, ++taken) {
+            const uint32_t x = q[i];
+            full += segs_of(x, g) - 1;
+            rest_it += ((uint64_t)(x ? ((x - 1) & mask) + 1 : 0u) + step) >> l;
+        }
+        const double scale = (double)n / (double)taken / (double)(64u >> l) / (double)slots;   // wave-items per wave
+        const uint32_t longest = (uint32_t)((((uint64_t)(qmax < mask ? qmax : mask) + 1) + step) >> l);
+        const double p0 = (double)taken * scale, passes = (double)full * scale + p0;
+        const double it = ((double)full * (double)((mask >> l) + 1) + (double)rest_it) * scale;   // iterations per wave
+        const double least = (double)longest * pc.floor + pc.item;
+        const double done = (double)(uint64_t)passes, part = passes - done;
+        const double w = 1.0 - pc.slope * (1.0 - part), share = w > pc.floor ? w : pc.floor;
+        double t;
+        if (passes < 1.0) {
+            t = it / passes * share + pc.item;
+        } else {
+            const double last = p0 >= part ? 0.7 * (double)rest_it / (double)taken : (double)((mask >> l) + 1);
+            t = it - part * last + done * pc.item + (part > 0 ? last * share + pc.item : 0.0);
+        }
+        return t > least ? t : least;
+    };
+    uint32_t ll = 6, lg = lg0;
+    double best = -1;
+    for (uint32_t l = 6; l >= 4; --l)
+        for (uint32_t g = lg0 < 5 ? 5 : lg0;; --g) {   // (1u << g of short chains: whole chains)
+            const double c = ragged_cost(l, g);
+            if (best < 0 || c < best) {
+                best = c;
+                ll = l;
+                lg = g;
+            }
+            if (g <= l + 2 || blocks >> g >= (8 * slots) << (6 - l))
+                break;
+        }
+    if (lg > lg0)
+        lg = lg0;
     auto items_at = [&](uint32_t g) {
         uint64_t t = 0;
         for (uint64_t i = 0; i < n; ++i)
             t += segs_of(q[i], g);
         return t;
     };
-    const uint32_t lg_min = ll + 2 < lg0 ? ll + 2 : lg0;
-    const uint64_t want_items = (4 * slots) << (6 - ll);   // 4 wave-items of 64 / 2^ll items per wave
-    // The segment size is the largest 2^lg (lg_min <= lg <= lg0) that still gives
-    // want_items items, else 2^lg_min. The item count falls as lg grows, so the
-    // search starts from an estimate (a chain adds about x / 2^lg + 1/2 items) and
-    // steps to the answer: one or two passes over the chains instead of one per
-    // candidate size.
-    uint32_t lg = lg0;
-    {
-        const uint64_t rest = want_items > n / 2 ? want_items - n / 2 : 1;
-        uint32_t ge = 0;
-        while (ge < 31 && ((uint64_t)blocks >> (ge + 1)) >= rest)
-            ++ge;
-        lg = ge < lg_min ? lg_min : (ge > lg0 ? lg0 : ge);
-    }
-    uint64_t n_items = items_at(lg);
-    if (n_items >= want_items) {
-        while (lg < lg0) {
-            const uint64_t up = items_at(lg + 1);
-            if (up < want_items)
-                break;
-            ++lg;
-            n_items = up;
-        }
-    } else {
-        while (lg > lg_min && n_items < want_items)
-            n_items = items_at(--lg);
-    }
+    const uint64_t n_items = items_at(lg);
     if (n_items > 0xFFFFFFFFull)
         return fail(FASTRACK_EINVAL, "more than 2^32-1 work items");
 

@@ -268,14 +268,4 @@ __device__ __forceinline__ u4 xor4(const u4 &a, const u4 &b)
     return r;
 }
 
-// XOR of a value over the 64 lanes of a wave; every lane receives the result.
-__device__ inline u4 wave_xor(u4 v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        for (int j = 0; j < 4; ++j)
-            v.w[j] ^= __shfl_xor(v.w[j], off, 64);
-    return v;
-}
-
 }  // namespace fastrack
