@@ -439,7 +439,7 @@ void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_
     p.seg_log2 = lg;
     p.segs_full = (uint32_t)((qc + (1ull << lg) - 1) >> lg);
     p.segs_last = (uint32_t)((p.q_last + (1ull << lg) - 1) >> lg);
-    p.segs_recip = p.segs_full > 1 ? (uint32_t)((1ull << 32) / p.segs_full) : 0xFFFFFFFFu;
+    p.segs_recip = div_recip_of(p.segs_full);
     p.n_items = (n - 1) * p.segs_full + p.segs_last;
 }
 

@@ -291,14 +291,8 @@ __device__ __forceinline__ ItemPos item_pos(const GcmLaunch &p, uint64_t item)
         r.tail = (uint32_t)(rc.len & 15);
     } else {
         const uint32_t it32 = (uint32_t)item;   // the host keeps a launch's items below 2^32
-        // it32 / segs_full with floor(2^32 / segs_full) (2^32 - 1 for 1): at most 2 too small
-        r.chain = __umulhi(it32, p.segs_recip);
+        r.chain = div_recip(it32, p.segs_full, p.segs_recip);
         r.s = it32 - r.chain * p.segs_full;
-        for (int fix = 0; fix < 2; ++fix) {
-            const uint32_t up = r.s >= p.segs_full ? 1u : 0u;
-            r.chain += up;
-            r.s -= up ? p.segs_full : 0u;
-        }
         const bool last = r.chain == p.n_chains - 1;
         r.q = last ? p.q_last : p.qc;
         r.S = last ? p.segs_last : p.segs_full;
@@ -353,7 +347,7 @@ constexpr uint32_t kWgMaskBase = kWgTagBase + 32;                     // uint4 i
 static_assert(kWavesPerWg <= 16 && kWavesPerWg % 4 == 0, "one workgroup-combine slot per wave");
 constexpr uint32_t kLdsBytes = (128 + 8 * kTreeLds) * 1024 + 512 + 1024 + 64;
 static_assert(kTBase * 16 == 0x10000, "one address byte places the T tables");
-// Modes without data AES: the GHASH table, T0 (for the J0 masks) and the lane-combine tables.
+// Modes without data AES: the GHASH table, T0 (for the J0 masks) and the lane-combine tables, 89 KiB.
 constexpr uint32_t kT0GhashOnly = 4096;         // uint4 index: 64 KiB
 constexpr uint32_t kTreeBaseGhashOnly = 4160;   // 65 KiB
 constexpr uint32_t kLdsGhashOnly = (65 + 8 * kTreeLds) * 1024 + 64;
@@ -500,10 +494,10 @@ __device__ inline u4 group_mul_tab4(const u4 &x, const Tab4 *__restrict__ t, uin
 // eight m (of M = L/8) multiplies its sum by H^(8 (M-1-m) + 2) in the same way, four
 // positions a lane, from the key's tables in global memory, and the item XOR-sums all its
 // lanes. Bound by latency: 16 + 8 + 4 lookups in LDS and 4 in global memory a lane in five
-// dependent batches. The form this replaces let one lane of each group look up all 32
-// positions (three levels, a last product by H^2: 128 LDS reads a wave in 16 batches, and
-// as the LDS serves a wave's 16-byte reads 16 lanes at a time, nearly as costly as with all
-// lanes active).
+// dependent batches: 1.1 us with the CU nearly idle, 1.7 with every wave of a 64 MiB launch
+// at its tail. With one lane of each group looking up all 32 positions (three levels, a last
+// product by H^2: 128 LDS reads a wave in 16 batches, and as the LDS serves a wave's 16-byte
+// reads 16 lanes at a time, nearly as costly as with all lanes active) it took 3.1 and 3.6 us.
 template <int CTRL>
 __device__ __forceinline__ u4 dpp4(const u4 &x)
 {
@@ -1223,7 +1217,11 @@ __device__ __forceinline__ void gcm_body(const GcmLaunch &p)
             // take no branches, so the scheduler mixes the GHASH lookups into the AES
             // rounds (the product acc . H^L waits for nothing in the iteration) and the load
             // of d has the whole iteration to arrive. The others, at the ends of a segment,
-            // are taken one at a time with every check.
+            // are taken one at a time with every check. An iteration is bound by the LDS (197
+            // 4-byte lookups at 2.0 CU-cycles and 16 of 16 bytes at 5: 474 per 64 blocks) with
+            // the VALU close behind (about 430 instructions, 0.6 to 1.05 cycles each), and the
+            // clock gives way to the power of both: 1 GiB of 1 MiB chains took 575 cycles per 64
+            // blocks with every check in every iteration, 532 so, the clock 2.17 -> 2.10 GHz.
             uint32_t k_a = Ku, k_b = Ku;
             if constexpr (kAes) {
                 const int first = pad - (int)jl;   // the lane's first block is in iteration ceil(first / L)

@@ -27,13 +27,27 @@ enum GcmMode : int {
     kApplyKs = 4,     // out = in XOR a precomputed keystream `ks`, GHASH over `in`, tag check
 };
 
-// Workgroups of the streaming kernel per CU: the modes with data AES take 152
-// KiB of a CU's LDS; the GHASH-only modes take 113 KiB (the GHASH table, a
-// plain T0 and the six lane-combine tables) and also run one 1024-thread
-// workgroup, 16 waves, per CU.
+// Workgroups of the streaming kernel per CU in its grid: one 1024-thread workgroup, 16 waves.
+// The fused mode takes 152 KiB of a CU's LDS, the AES-only modes 64 KiB (the T-tables), the
+// GHASH-only modes 89 KiB (the GHASH table, a plain T0 and the lane-combine tables).
 constexpr int gcm_wgs_per_cu(int mode)
 {
     return (mode == kVerify || mode == kApplyKs) && kGcmWavesPerWg < 16 ? 16 / kGcmWavesPerWg : 1;
+}
+
+// n / d with recip = floor(2^32 / d), 2^32 - 1 for d = 1 (what div_recip_of returns): recip is
+// less than one below 2^32 / d, so n recip / 2^32 is less than one below n / d and the
+// quotient at most one too small. (The kernels take an item's chain so: a 32-bit division is
+// a chain of some 30 instructions at the start of every item.)
+__host__ __device__ constexpr uint32_t div_recip_of(uint32_t d)
+{
+    return d > 1 ? (uint32_t)((1ull << 32) / d) : 0xFFFFFFFFu;
+}
+
+__host__ __device__ constexpr uint32_t div_recip(uint32_t n, uint32_t d, uint32_t recip)
+{
+    const uint32_t q = (uint32_t)(((uint64_t)n * recip) >> 32);
+    return q + (n - q * d >= d ? 1u : 0u);
 }
 
 // One chain of a ragged launch: bytes [off, off + len) of the buffers (off a
@@ -69,7 +83,7 @@ struct GcmLaunch {
     uint32_t lanes_log2;        // lanes per item: 4 (16), 5 (32) or 6 (64); the Horner stride
     uint32_t segs_full;         // segments of a full chain
     uint32_t segs_last;         // segments of the last chain
-    uint32_t segs_recip;        // floor(2^32 / segs_full), 2^32 - 1 for 1
+    uint32_t segs_recip;        // div_recip_of(segs_full)
     // Set by the launch: the wave-items (64 >> lanes_log2 items each) and how many waves of
     // the grid take one more of them than the others.
     uint32_t wave_items, last_pass;
