@@ -118,8 +118,8 @@ int fastrack_gcm_decrypt_verify(const uint8_t *key, const uint8_t *base_iv, uint
  * tables.
  * EINVAL as fastrack_gcm_decrypt_verify, and also when a launch would need more
  * than FASTRACK_NOALLOC_MAX_PARTIALS partial slots (items + chains); the
- * library's work planner stays below about 200,000 for every size, so this
- * limit is a guard, not a size cap callers meet.
+ * library's work planner cuts chains into segments only as far as that holds,
+ * so this limit is a guard, not a size cap callers meet.
  */
 #define FASTRACK_NOALLOC_SCRATCH_BYTES (5u << 20)
 #define FASTRACK_NOALLOC_MAX_PARTIALS 230240u

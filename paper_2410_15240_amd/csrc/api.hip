@@ -270,6 +270,17 @@ int scratch_for(int dev, hipStream_t s, size_t bytes, void **out)
     return FASTRACK_OK;
 }
 
+// True if launches on a stream being captured must do without scratch of `bytes`: none can
+// be allocated there.
+bool capture_lacks_scratch(int dev, hipStream_t s, size_t bytes)
+{
+    for (auto &x : g_scratch)
+        if (x.dev == dev && x.stream == s && x.bytes >= bytes)
+            return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 // Pinned host staging of at least `bytes` for (device, stream), free to overwrite:
 // the upload that last read it has completed. The buffers are used in turn, so the
 // tables of the next calls are written while earlier uploads are pending.
@@ -388,8 +399,12 @@ double plan_cost(const PlanCost &pc, uint64_t n, uint64_t qc, uint64_t q_last, u
 // chains, so that its set-up and tail are paid once for all of them; 64 lanes
 // and segments of few blocks give every wave work when the chains are few; and
 // wave-items that do not divide evenly over the waves leave a last pass in which
-// most of them idle.
-void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t slots, GcmLaunch &p)
+// most of them idle. Chains are cut only if the items and chains together stay within
+// max_partials, the slots of their partials and masks (0: whole chains).
+constexpr uint64_t kMaxPartials = FASTRACK_NOALLOC_MAX_PARTIALS;
+
+void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t slots, GcmLaunch &p,
+               uint64_t max_partials = kMaxPartials)
 {
     const uint64_t n = (len + chain_bytes - 1) / chain_bytes;
     const uint64_t qc = chain_bytes / 16;
@@ -403,6 +418,7 @@ void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_
     if (lg0 > 31)
         lg0 = 31;
     auto items_at = [&](uint32_t g) { return n * ((qc + (1ull << g) - 1) >> g); };
+    auto fits = [&](uint32_t g) { return items_at(g) == n || items_at(g) + n <= max_partials; };
     // Segments have at least 4 iterations. For each number of lanes the candidates run
     // from whole chains to the first segment length with 8 wave-items per wave (shorter
     // ones only add tails).
@@ -410,7 +426,7 @@ void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_
     uint32_t ll = 6, lg = lg0;
     double best = -1;
     for (uint32_t l = 6; l >= 4; --l)
-        for (uint32_t g = lg0;; --g) {
+        for (uint32_t g = lg0; fits(g); --g) {
             const double c = plan_cost(pc, n, qc, p.q_last, l, g, slots);
             if (best < 0 || c < best) {
                 best = c;
@@ -428,12 +444,12 @@ void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_
         // 18.2 with 128, 19.5 with 64 (whose 6-bit segment weights cost more than the
         // shorter items gain); one 1 MiB chain 22.3 -> 19.6 us; 4 MiB of 1 MiB chains
         // 23.7 -> 21.4 us.
-        while (lg > (uint32_t)kMinSmallSegLog2 && items_at(lg) < slots / 2 &&
+        while (lg > (uint32_t)kMinSmallSegLog2 && items_at(lg) < slots / 2 && fits(lg - 1) &&
                ((qc + (1ull << (lg - 1)) - 1) >> (lg - 1)) <= kMaxSmallSegs)
             --lg;
     // The smallest, with at most one 64-block item per CU: one iteration each (an image of
     // 150,528 bytes in 16 chains).
-    if (ll == 6 && lg == (uint32_t)kMinSmallSegLog2 && items_at(6) <= slots / kGcmWavesPerWg)
+    if (ll == 6 && lg == (uint32_t)kMinSmallSegLog2 && items_at(6) <= slots / kGcmWavesPerWg && fits(6))
         lg = 6;
     p.lanes_log2 = ll;
     p.seg_log2 = lg;
@@ -494,7 +510,16 @@ int run_gcm(bool encrypt, GcmMode mode, const KeyCtx *ctx, const uint8_t *base_i
 {
     GcmLaunch p;
     std::memset(&p, 0, sizeof p);
-    make_plan(mode, len, chain_bytes, chain_base, (uint64_t)num_cu * kGcmWavesPerWg * gcm_wgs_per_cu(mode), p);
+    const uint64_t slots = (uint64_t)num_cu * kGcmWavesPerWg * gcm_wgs_per_cu(mode);
+    make_plan(mode, len, chain_bytes, chain_base, slots, p);
+    // The scratch of any cut launch is taken at the size that holds every one, so that a
+    // stream that ran one can be captured with others. Under capture and with none, chains
+    // of up to 4 KiB, and of any size if there is one for every wave, run whole.
+    constexpr size_t kScratchBytes = (size_t)kMaxPartials * 16;
+    const bool ghash = mode == kFused || mode == kVerify || mode == kApplyKs;
+    if (ghash && p.n_items > p.n_chains && !fixed_scratch && (p.qc <= 256 || p.n_chains >= slots) &&
+        capture_lacks_scratch(dev, s, kScratchBytes))
+        make_plan(mode, len, chain_bytes, chain_base, slots, p, 0);
     if (p.n_items > 0xFFFFFFFFull)   // the kernel indexes a launch's items in 32 bits
         return fail(FASTRACK_EINVAL, "more than 2^32-1 work items in one launch");
     p.ctx = ctx;
@@ -524,7 +549,6 @@ int run_gcm(bool encrypt, GcmMode mode, const KeyCtx *ctx, const uint8_t *base_i
         }
         return FASTRACK_OK;
     }
-    const bool ghash = mode == kFused || mode == kVerify || mode == kApplyKs;
     p.split = ghash && p.n_items > p.n_chains ? 1u : 0u;
     if (p.split) {   // chains cut into segments: per-item partials and per-chain masks
         if (fixed_scratch) {   // the caller's fixed area (allocation-free entry point)
@@ -534,7 +558,8 @@ int run_gcm(bool encrypt, GcmMode mode, const KeyCtx *ctx, const uint8_t *base_i
             p.partials = fixed_scratch;
         } else {
             void *sc = nullptr;
-            int rc = scratch_for(dev, s, (size_t)(p.n_items + p.n_chains) * 16, &sc);
+            const size_t bytes = (size_t)(p.n_items + p.n_chains) * 16;
+            int rc = scratch_for(dev, s, bytes > kScratchBytes ? bytes : kScratchBytes, &sc);
             if (rc)
                 return rc;
             p.partials = reinterpret_cast<uint4 *>(sc);
@@ -1433,7 +1458,8 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     // the units of plan_cost: the items' iterations and about one per item for set-up and tail
     // over the waves, and a last, partial pass of the shortest items. (1024 samples of 16
     // chains: 16 lanes and 256 blocks, 186 us; 128 blocks 193, 512 188. 256 samples: 32 lanes
-    // and 512 blocks, 63 us; 256 blocks 66, 64 lanes and 256 blocks 72.)
+    // and 512 blocks, 63 us; 256 blocks 66, 64 lanes and 256 blocks 72; with a tag kernel of
+    // 64 lanes per chain.)
     const uint64_t slots = (uint64_t)ncu * kGcmWavesPerWg;
     uint32_t lg0 = ceil_log2(qmax > 0 ? qmax : 1);
     if (lg0 > 31)

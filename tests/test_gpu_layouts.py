@@ -77,3 +77,35 @@ def test_layout_matches_the_oracle(F, length, chain, abytes, want):
     got = F.apply_verify(w.key, w.base_iv, chain, d_ct, ks, d_tags, d_aad)
     assert np.array_equal(host(got[1]), ok)
     assert np.array_equal(host(got[0]), pt)
+
+
+def test_captured_on_a_stream_without_scratch(F):
+    """A graph captured on a stream that no call has used yet, where the plan would cut the
+    chains and nothing can be allocated: they run whole, and every replay gives the eager
+    results."""
+    import torch
+    n, blocks = 4111, 289
+    length, chain = n * blocks * 16, blocks * 16
+    w = W.random_case(5, length, chain)
+    ct, tags = oracle.chains_encrypt(w.key, w.base_iv, chain, w.payload, None, 0)
+    tags = tags.copy()
+    W.flip_bit(tags.reshape(-1)[77 * 16:], 77)
+    want_ok = np.ones(n, np.uint8)
+    want_ok[77] = 0
+    d_ct, d_tags = dev(ct), dev(tags)
+    pt, ok = F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags)
+    F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags)
+    assert np.array_equal(host(ok), want_ok)
+    out, flags = torch.zeros_like(pt), torch.zeros_like(ok)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags, out=out, ok=flags)
+    for _ in range(3):
+        out.zero_()
+        flags.zero_()
+        g.replay()
+        assert np.array_equal(host(flags), want_ok)
+        assert np.array_equal(host(out), w.payload)
+        F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags)

@@ -112,3 +112,12 @@ def test_plan_rejects_bad_arguments(L, args):
     out = (ctypes.c_uint64 * 7)()
     assert L.fastrack_plan(*args, out) == -1
     assert L.fastrack_plan(16, 16, 256, None) == -1
+
+
+@pytest.mark.parametrize("n,blocks", [(82064, 427), (4595, 1704572), (25734, 38165), (472, 32954200), (43, 181474293),
+                                      (58267, 172654), (111111, 300), (3000, 100000), (1, (1 << 32) - 2)])
+def test_cut_chains_fit_the_fixed_partials(L, n, blocks):
+    """Launches that cut chains keep within the allocation-free area's partial slots (these
+    are sizes whose least estimated time lies beyond it)."""
+    p = plan(L, n * blocks * 16, blocks * 16)
+    assert not p["split"] or p["items"] + n <= 230240
