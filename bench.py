@@ -46,8 +46,8 @@ PRE_S, PRE_MAX_CALLS = 0.05, 2000
 ROTATE = 4                       # buffer sets the per-size timings cycle through
 # LDS reads per 64 blocks of the streaming kernel's main loop and their measured cost
 # (CU-cycles per wave instruction, conflict-free, 16 waves per CU)
-LDS_T_READS, LDS_T_CYCLES = 197, 2.8
-LDS_GH_READS, LDS_GH_CYCLES = 16, 5.5
+LDS_T_READS, LDS_T_CYCLES = 197, 2.0
+LDS_GH_READS, LDS_GH_CYCLES = 16, 5.0
 
 KiB, MiB, GiB = 1024, 1 << 20, 1 << 30
 
@@ -198,8 +198,8 @@ def main():
         % (value, ms_per_step, launch_ms * 1e3, per_size_mean_ms * 1e3, ["%.2f" % c for c in clocks], copy_gbs))
     sq = sq_profile("decrypt")
     # The LDS bound of the main loop: per 64 blocks (one wave-iteration) 197 conflict-free
-    # 32-bit T-table reads at 2.8 CU-cycles each and 16 conflict-free 16-byte GHASH reads
-    # at 5.5 (microbenchmarks on the box), over 256 CUs at the clock the probe measured.
+    # 32-bit T-table reads at 2.0 CU-cycles each and 16 conflict-free 16-byte GHASH reads
+    # at 5.0 (microbenchmarks, waves running freely), over 256 CUs at the clock the probe measured.
     lds_cycles = LDS_T_READS * LDS_T_CYCLES + LDS_GH_READS * LDS_GH_CYCLES
     clk = float(np.mean(clocks))
     bound_us = L / 16 / 64 / 256 * lds_cycles / (clk * 1e3)

@@ -494,10 +494,9 @@ __device__ inline u4 group_mul_tab4(const u4 &x, const Tab4 *__restrict__ t, uin
 // eight m (of M = L/8) multiplies its sum by H^(8 (M-1-m) + 2) in the same way, four
 // positions a lane, from the key's tables in global memory, and the item XOR-sums all its
 // lanes. Bound by latency: 16 + 8 + 4 lookups in LDS and 4 in global memory a lane in five
-// dependent batches: 1.1 us with the CU nearly idle, 1.7 with every wave of a 64 MiB launch
-// at its tail. With one lane of each group looking up all 32 positions (three levels, a last
+// dependent batches: 1.2 to 1.9 us of a launch's tail. With one lane of each group looking up all 32 positions (three levels, a last
 // product by H^2: 128 LDS reads a wave in 16 batches, and as the LDS serves a wave's 16-byte
-// reads 16 lanes at a time, nearly as costly as with all lanes active) it took 3.1 and 3.6 us.
+// reads 16 lanes at a time, nearly as costly as with all lanes active) it took 3.1 us.
 template <int CTRL>
 __device__ __forceinline__ u4 dpp4(const u4 &x)
 {
@@ -736,7 +735,7 @@ __device__ __forceinline__ u4 ghash_step(const char *lds, const u4 &acc, const u
 // GcmMode: which of keystream, data XOR and GHASH + tag the launch computes.
 // RAG: chains of their own offsets and lengths from the launch's chain table.
 template <bool ENC, int LL, bool SPLIT, int MODE, bool RAG>
-__device__ __forceinline__ void gcm_body(const GcmLaunch &p)
+__global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) void gcm_kernel(GcmLaunch p)
 {
     constexpr bool kGhash = MODE == kFused || MODE == kVerify || MODE == kApplyKs;   // GHASH + tag
     constexpr bool kAes = MODE == kFused || MODE == kCtr || MODE == kKeystream;      // keystream by AES
@@ -814,7 +813,10 @@ __device__ __forceinline__ void gcm_body(const GcmLaunch &p)
 
     const uint32_t lb = ((lane & 31) << 2) | (kT * 16);
     const uint32_t lc0 = lb, lc1 = lb | 0x80u;
-    const uint32_t m1 = MODE == kCtr && LL == 6 ? 0xFF00u : byte1_mask();   // (see ctr64_kernel)
+    // CTR with 64 lanes per item takes 48 VGPRs with the mask as a literal and 49 with it in a
+    // register; with 48 its workgroup fits a CU beside one of the verify kernel's (eager,
+    // 64 MiB at 64 KiB chains: 94.3 -> 83.9 us a call).
+    const uint32_t m1 = MODE == kCtr && LL == 6 ? 0xFF00u : byte1_mask();
     const GhLane gk = ghash_lane(lane);
     // The 60 round-key words are uniform: they stay in scalar registers (the XORs
     // take them as scalar operands), which keeps the kernel within the 128 VGPRs
@@ -1351,20 +1353,6 @@ __device__ __forceinline__ void gcm_body(const GcmLaunch &p)
     }
 }
 
-template <bool ENC, int LL, bool SPLIT, int MODE, bool RAG>
-__global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) void gcm_kernel(GcmLaunch p)
-{
-    gcm_body<ENC, LL, SPLIT, MODE, RAG>(p);
-}
-
-// CTR with 64 lanes per item in 48 VGPRs (47 and the one that holds spilled SGPRs; left
-// alone the body takes 49), so that its workgroup
-// shares a CU with one of the verify kernel's.
-__global__ __launch_bounds__(kThreads, kWavesPerWg / 4) __attribute__((amdgpu_num_vgpr(47))) void ctr64_kernel(GcmLaunch p)
-{
-    gcm_body<false, 6, false, kCtr, false>(p);
-}
-
 // Chains cut into segments: T = mask xor the XOR of the chain's weighted
 // partials. 2^GL lanes per chain: they load the partials side by side and
 // XOR-sum them. 64 lanes where chains have many segments, 8 where they have few on the
@@ -1498,8 +1486,6 @@ static hipError_t launch_mode(const GcmLaunch &p, int num_cu, hipStream_t s)
         hipLaunchKernelGGL((gcm_kernel<ENC, 5, false, MODE, RAG>), dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
     else if (p.lanes_log2 == 5)
         hipLaunchKernelGGL((gcm_kernel<ENC, 5, ghash, MODE, RAG>), dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
-    else if (MODE == kCtr)
-        hipLaunchKernelGGL(ctr64_kernel, dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
     else if (!split)
         hipLaunchKernelGGL((gcm_kernel<ENC, 6, false, MODE, RAG>), dim3((uint32_t)wgs), dim3(kThreads), 0, s, q);
     else

@@ -8,8 +8,8 @@
 
 namespace fastrack {
 
-// Threads per workgroup of the streaming kernel. Its 160 KiB of LDS allow one
-// workgroup per CU, so this is also the number of resident threads per CU:
+// Threads per workgroup of the streaming kernel. Of the fused mode the 152 KiB of tables
+// allow one workgroup in a CU's 160 KiB, so this is also the number of resident threads:
 // 16 waves, four per SIMD, which the kernel's register use (at most 128 VGPRs)
 // allows. More waves per SIMD hide more of the LDS latency of the table lookups.
 #ifndef FT_GCM_THREADS
