@@ -440,16 +440,25 @@ void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_
         // Small launches, where even 256-block segments leave more than half of the
         // waves idle: shorter segments, down to two iterations of the 64 lanes, while
         // a chain stays at most 512 segments (the tag sums and segment weights grow
-        // with the count). 1 MiB of 64 KiB chains: 21.8 us with 256-block segments,
-        // 18.2 with 128, 19.5 with 64 (whose 6-bit segment weights cost more than the
-        // shorter items gain); one 1 MiB chain 22.3 -> 19.6 us; 4 MiB of 1 MiB chains
-        // 23.7 -> 21.4 us.
+        // with the count). 1 MiB of 64 KiB chains: 16.7 us with 256-block segments, 13.5
+        // with 128; one 1 MiB chain 17.5 and 14.9; 4 MiB of 1 MiB chains 18.9 and 18.0.
         while (lg > (uint32_t)kMinSmallSegLog2 && items_at(lg) < slots / 2 && fits(lg - 1) &&
                ((qc + (1ull << (lg - 1)) - 1) >> (lg - 1)) <= kMaxSmallSegs)
             --lg;
-    // The smallest, with at most one 64-block item per CU: one iteration each (an image of
-    // 150,528 bytes in 16 chains).
-    if (ll == 6 && lg == (uint32_t)kMinSmallSegLog2 && items_at(6) <= slots / kGcmWavesPerWg && fits(6))
+    // The smallest in segments of one iteration: every wave-item saves the second one (1.3
+    // us), but more of them share a CU, each with a tail. Decrypt + verify and encrypt + tag
+    // up to two for every CU (512 KiB of 64 KiB chains 12.9 -> 11.4 us, one 400,000-byte chain
+    // 14.1 -> 13.4). 1 MiB would still gain (13.4 -> 12.1), but its cut into two-iteration
+    // segments is a published plan; above, it turns (1.5 MB of 300,000-byte chains
+    // 14.7 -> 15.0, 3 MiB of 10,000-byte ones 15.1 -> 16.6). The AES-only modes have no tail:
+    // up to one for every wave (1 MiB 6.9 -> 5.4 us, 3 MiB of 10,000-byte chains 8.1 -> 7.8).
+    // The modes without AES, with short iterations, up to one for every CU (512 KiB
+    // keystream-apply 8.8 -> 9.2 us).
+    const uint64_t max_single = mode == kFused                         ? slots / (kGcmWavesPerWg / 2)
+                                : mode == kCtr || mode == kKeystream ? slots
+                                                                     : slots / kGcmWavesPerWg;
+    if (ll == 6 && lg == (uint32_t)kMinSmallSegLog2 && items_at(6) <= max_single && ((qc + 63) >> 6) <= kMaxSmallSegs &&
+        fits(6))
         lg = 6;
     p.lanes_log2 = ll;
     p.seg_log2 = lg;

@@ -28,6 +28,8 @@ LAYOUTS = [
     (12876048, 784, 0, (5, 0, 1)),
     (35867559, 3888, 32, (6, 0, 1)),
     (14959, 7248, 5, (6, 1, 0)),
+    (440001, 60016, 5, (6, 1, 0)),
+    (2999999, 10000, 7, (6, 1, 0)),
 ]
 
 
