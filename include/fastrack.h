@@ -326,8 +326,10 @@ int fastrack_pipeline_d2h_mode(const uint8_t *key, const uint8_t *base_iv, uint6
  * d_ct and d_pt (or d_pt and d_ct) may be NULL when every chain is empty.
  * The host arrays are read during the call only. The chain table goes to the
  * device through a per-stream pinned staging buffer that the library owns; a
- * later call on the same stream reuses it once the device has read it.
- * EINVAL: as for fastrack_gcm_decrypt_verify / fastrack_gcm_encrypt_tag, plus
+ * later call on the same stream reuses it once the device has read it: a ragged
+ * call cannot be captured into a graph and is refused on a capturing stream.
+ * EINVAL: as for fastrack_gcm_decrypt_verify / fastrack_gcm_encrypt_tag, plus a
+ * capturing stream,
  * NULL h_chain_off/h_chain_len with n_chains > 0, a misaligned, decreasing or
  * overlapping offset, an oversized chain, more than 2^32-1 chains or work items.
  * n_chains == 0 is a successful no-op.

@@ -1450,12 +1450,19 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     if (encrypt ? !tags_out : (!tags_in || !ok))
         return fail(FASTRACK_EINVAL, encrypt ? "d_tags must be non-NULL" : "d_tags and d_ok must be non-NULL");
 
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    // A replay would read the staging buffer and write the table slot that later calls on the
+    // stream reuse, and would run this call's kernels on another call's tables.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+        return fail(FASTRACK_EINVAL, "ragged calls cannot be captured: their chain tables are staged in buffers that "
+                                     "later calls reuse");
+
     std::lock_guard<std::mutex> lk(g_mu);
     int dev, ncu;
     int rc;
     if ((rc = current_device(&dev, &ncu)))
         return rc;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const KeyCtx *ctx;
     if ((rc = key_ctx(key, s, dev, &ctx)))
         return rc;

@@ -1,0 +1,381 @@
+// The library's host code (api.hip) over a stand-in for the HIP runtime, on the CPU.
+//
+// Streams, events and host synchronisation are vector clocks: a stream's work carries
+// everything that is known to come before it, and an access to memory is a race if
+// another one to the same bytes, at least one of them a write, is not among that. Every
+// event that the host has not waited for counts as not yet done, so an order that only
+// holds on a fast GPU does not count. The kernels' launches are replaced by the accesses
+// they make, and a ragged launch's tables are checked to cut every chain into its blocks
+// exactly once. A capturing stream refuses what a captured stream cannot hold.
+//
+// Built with a plain C++ compiler; no device code is compiled and no GPU is used.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+
+#define __align__(n) __attribute__((aligned(n)))
+#define HIP_SYMBOL(x) (&(x))
+#include "api.hip"
+
+namespace {
+
+constexpr int kCtx = 40;   // clock entries: 0 is the host, the others streams
+typedef std::array<uint64_t, kCtx> Clock;
+
+struct Access {
+    uintptr_t b, e;
+    bool write;
+    int ctx;
+    uint64_t at;
+    const char *what;
+};
+
+struct Stream {
+    int ctx;
+    Clock vc{};
+    bool capturing = false;
+};
+
+int g_races, g_refused, g_thread, g_next_ctx = 1, g_ops;
+Clock g_host{};
+std::map<uintptr_t, Stream> g_streams;   // by handle; the per-thread handle by thread
+std::vector<Access> g_acc;
+std::map<uintptr_t, size_t> g_mem;
+GcmLaunch g_last;      // the last launch, and how it was asked for
+int g_last_mode;
+bool g_last_tables_ok;
+
+const uintptr_t kPerThread = 2;   // hipStreamPerThread
+
+void join(Clock &a, const Clock &b)
+{
+    for (int i = 0; i < kCtx; ++i)
+        a[i] = std::max(a[i], b[i]);
+}
+
+Stream &stream_at(hipStream_t s)
+{
+    uintptr_t h = (uintptr_t)s;
+    if (h == kPerThread)
+        h = 0x10000 + (uintptr_t)g_thread;
+    auto it = g_streams.find(h);
+    if (it == g_streams.end()) {
+        if (g_next_ctx == kCtx) {
+            printf("too many streams\n");
+            exit(2);
+        }
+        it = g_streams.emplace(h, Stream{g_next_ctx++}).first;
+    }
+    return it->second;
+}
+
+Stream &enqueue(hipStream_t s)
+{
+    Stream &st = stream_at(s);
+    ++g_ops;
+    ++g_host[0];
+    join(st.vc, g_host);
+    ++st.vc[st.ctx];
+    return st;
+}
+
+void touch(const void *p, uint64_t n, bool write, int ctx, const Clock &now, const char *what)
+{
+    const uintptr_t b = (uintptr_t)p, e = b + n;
+    for (const Access &a : g_acc)
+        if (a.b < e && b < a.e && (a.write || write) && a.at > now[a.ctx]) {
+            if (++g_races <= 5)
+                printf("race: %s against %s\n", what, a.what);
+        }
+    g_acc.push_back({b, e, write, ctx, now[ctx], what});
+    if (g_acc.size() > 20000)
+        g_acc.erase(g_acc.begin(), g_acc.begin() + 10000);
+}
+
+bool any_capturing()
+{
+    for (auto &s : g_streams)
+        if (s.second.capturing)
+            return true;
+    return false;
+}
+
+hipError_t refuse()
+{
+    ++g_refused;
+    return hipErrorStreamCaptureUnsupported;
+}
+
+struct Event {
+    Clock vc{};
+    bool recorded = false;
+    bool captured = false;
+};
+
+hipError_t alloc(void **p, size_t n)
+{
+    *p = aligned_alloc(256, (n + 255) & ~(size_t)255);
+    if (!*p)
+        return hipErrorOutOfMemory;
+    memset(*p, 0xA5, n);
+    g_mem[(uintptr_t)*p] = n;
+    return hipSuccess;
+}
+
+// A free is safe once the host knows that every access to the area is over.
+void release(void *p)
+{
+    if (!p)
+        return;
+    const size_t n = g_mem.at((uintptr_t)p);
+    touch(p, n, true, 0, g_host, "free");
+    g_acc.erase(std::remove_if(g_acc.begin(), g_acc.end(),
+                               [&](const Access &a) { return a.b < (uintptr_t)p + n && (uintptr_t)p < a.e; }),
+                g_acc.end());
+    g_mem.erase((uintptr_t)p);
+    free(p);
+}
+
+// The tables cut every chain into its segments: each item belongs to the chain that its
+// table entry names, is one of that chain's segments, and every segment has one item.
+bool tables_ok(const GcmLaunch &p)
+{
+    std::vector<uint8_t> seen((size_t)p.n_items, 0);
+    uint64_t items = 0;
+    for (uint32_t i = 0; i < p.n_chains; ++i) {
+        const RaggedChain &c = p.rchains[i];
+        const uint64_t q = (c.len + 15) / 16, seg = 1ull << p.seg_log2;
+        const uint64_t want = q ? (q + seg - 1) / seg : 1;
+        if (c.segs != want)
+            return false;
+        for (uint64_t s = 0; s < c.segs; ++s) {
+            const uint64_t it = s == 0 ? c.item0 : c.item_base + s;
+            if (it >= p.n_items || seen[it] || p.ritem_chain[it] != i)
+                return false;
+            seen[it] = 1;
+        }
+        items += c.segs;
+    }
+    return items == p.n_items;
+}
+
+}  // namespace
+
+extern "C" {
+const char *hipGetErrorString(hipError_t) { return "error of the stand-in runtime"; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceSynchronize()
+{
+    if (any_capturing())
+        return refuse();
+    for (auto &s : g_streams)
+        join(g_host, s.second.vc);
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) { return any_capturing() ? refuse() : alloc(p, n); }
+hipError_t hipFree(void *p)
+{
+    if (any_capturing())
+        return refuse();
+    release(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return any_capturing() ? refuse() : alloc(p, n); }
+hipError_t hipHostFree(void *p) { return hipFree(p); }
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = const_cast<void *>(s); return hipSuccess; }
+hipError_t hipMemset(void *, int, size_t) { return hipSuccess; }
+hipError_t hipMemsetAsync(void *p, int, size_t n, hipStream_t s)
+{
+    Stream &st = enqueue(s);
+    if (st.capturing)
+        return refuse();   // the library records no memory-set node
+    touch(p, n, true, st.ctx, st.vc, "memset");
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipErrorUnknown; }
+hipError_t hipMemGetAddressRange(hipDeviceptr_t *, size_t *, hipDeviceptr_t) { return hipErrorUnknown; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return hipErrorUnknown; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned)
+{
+    static uintptr_t next = 0x20000;
+    *s = reinterpret_cast<hipStream_t>(next++);
+    stream_at(*s);
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s)
+{
+    if (any_capturing())
+        return refuse();
+    join(g_host, stream_at(s).vc);
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st)
+{
+    *st = stream_at(s).capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
+{
+    *e = reinterpret_cast<hipEvent_t>(new Event);
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e)
+{
+    delete reinterpret_cast<Event *>(e);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t h, hipStream_t s)
+{
+    Event *e = reinterpret_cast<Event *>(h);
+    Stream &st = stream_at(s);
+    join(st.vc, g_host);
+    e->vc = st.vc;
+    e->recorded = true;
+    e->captured = st.capturing;
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t h, unsigned)
+{
+    Event *e = reinterpret_cast<Event *>(h);
+    Stream &st = stream_at(s);
+    if (e->recorded && st.capturing != e->captured)
+        return refuse();
+    if (e->recorded)
+        join(st.vc, e->vc);
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t h)
+{
+    Event *e = reinterpret_cast<Event *>(h);
+    if (e->captured)
+        return refuse();
+    for (int i = 0; i < kCtx; ++i)
+        if (e->recorded && e->vc[i] > g_host[i])
+            return hipErrorNotReady;
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t h)
+{
+    Event *e = reinterpret_cast<Event *>(h);
+    if (e->captured)
+        return refuse();
+    if (e->recorded)
+        join(g_host, e->vc);
+    return hipSuccess;
+}
+}  // extern "C"
+
+namespace fastrack {
+
+hipError_t launch_key_setup(const uint32_t *, KeyCtx *ctx, hipStream_t s)
+{
+    Stream &st = enqueue(s);
+    touch(ctx, sizeof *ctx, true, st.ctx, st.vc, "key set-up");
+    return hipSuccess;
+}
+hipError_t launch_upload(const void *src, void *dst, uint64_t n, hipStream_t s)
+{
+    touch(src, n, true, 0, g_host, "host's tables");   // written since the last synchronisation
+    Stream &st = enqueue(s);
+    touch(src, n, false, st.ctx, st.vc, "upload's read");
+    touch(dst, n, true, st.ctx, st.vc, "upload");
+    memcpy(dst, src, n);
+    return hipSuccess;
+}
+hipError_t launch_gcm(const GcmLaunch &p, bool, GcmMode mode, int, hipStream_t s)
+{
+    Stream &st = enqueue(s);
+    touch(p.ctx, sizeof *p.ctx, false, st.ctx, st.vc, "kernel's key");
+    g_last = p;
+    g_last_mode = mode;
+    g_last_tables_ok = true;
+    if (p.rchains) {
+        touch(p.rchains, p.n_chains * sizeof(RaggedChain), false, st.ctx, st.vc, "kernel's chain table");
+        touch(p.ritem_chain, p.n_items * 4, false, st.ctx, st.vc, "kernel's item table");
+        g_last_tables_ok = tables_ok(p);
+    }
+    if (p.split)
+        touch(p.partials, (p.n_items + p.n_chains) * 16, true, st.ctx, st.vc, "partials");
+    return hipSuccess;
+}
+hipError_t launch_seq_ghash(const GcmLaunch &, bool, hipStream_t s) { enqueue(s); return hipSuccess; }
+hipError_t launch_clock_probe(uint64_t, uint32_t, uint64_t *, hipStream_t) { return hipErrorUnknown; }
+hipError_t launch_bs_keystream(const GcmLaunch &, int, hipStream_t s) { enqueue(s); return hipSuccess; }
+
+}  // namespace fastrack
+
+namespace {
+
+uint8_t kKey[32], kIv[12];
+uint8_t *const A = reinterpret_cast<uint8_t *>(0x1000000000ull);   // never dereferenced
+int g_fails;
+
+#define EXPECT(c)                                                                   \
+    do {                                                                            \
+        if (!(c)) {                                                                 \
+            ++g_fails;                                                              \
+            printf("line %d: %s (last error: %s)\n", __LINE__, #c, g_err.c_str());  \
+        }                                                                           \
+    } while (0)
+
+hipStream_t S(uintptr_t h) { return reinterpret_cast<hipStream_t>(h); }
+
+int ragged(const std::vector<uint64_t> &lens, uintptr_t stream)
+{
+    std::vector<uint64_t> off(lens.size());
+    uint64_t o = 0;
+    for (size_t i = 0; i < lens.size(); ++i) {
+        off[i] = o;
+        o += (lens[i] + 15) & ~15ull;
+    }
+    return fastrack_gcm_decrypt_verify_ragged(kKey, kIv, off.data(), lens.data(), lens.size(), A, A, nullptr, 0, A, A,
+                                              S(stream));
+}
+
+int uniform(uint64_t len, uint64_t chain, uintptr_t stream)
+{
+    return fastrack_gcm_decrypt_verify(kKey, kIv, chain, A, len, A, nullptr, 0, A, A, 0, S(stream));
+}
+
+// A ragged call on a capturing stream: refused before it changes anything or enqueues
+// anything, with the ring in each of its states; the calls after the capture work.
+void capture_ragged()
+{
+    const std::vector<uint64_t> small(20, 1000), large(6000, 1000), cut(16, 1 << 20);
+    for (const auto &lens : {small, large, cut})
+        for (int before = 0; before < 7; ++before) {
+            fastrack_shutdown();
+            for (int i = 0; i < before; ++i)
+                EXPECT(ragged(small, 0x100) == 0);
+            Stream &st = stream_at(S(0x100));
+            st.capturing = true;
+            const int ops = g_ops, refused = g_refused;
+            EXPECT(ragged(lens, 0x100) == FASTRACK_EINVAL);
+            EXPECT(g_ops == ops && g_refused == refused);
+            st.capturing = false;
+            for (int i = 0; i < 6; ++i)
+                EXPECT(ragged(i & 1 ? small : lens, 0x100) == 0 && g_last_tables_ok);
+        }
+    EXPECT(g_races == 0);
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "capture_ragged")
+        capture_ragged();
+    else
+        return 2;
+    fastrack_shutdown();
+    printf("%s: %d failures, %d races\n", what.c_str(), g_fails, g_races);
+    return g_fails || g_races;
+}

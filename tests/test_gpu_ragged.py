@@ -206,3 +206,37 @@ def test_sample_batch_full_size(F):
         o, l = int(off[i]), int(ln[i])
         want, ok_i = oracle.gcm_decrypt(w.key, oracle.chain_iv(w.base_iv, i), got_ct[o:o + l], got_tags[i], aad[i])
         assert not ok_i and np.array_equal(got_pt[o:o + l], want)
+
+
+def test_capture_is_refused(F):
+    """A ragged call on a capturing stream raises, whether or not the stream's tables are set up;
+    the capture goes on without it and the calls after it work."""
+    import torch
+    w = W.ragged_case(4001, lens_of(10, 60, 0, 3000), None, 3)
+    off, ln = w.extra["chain_off"], w.extra["chain_len"]
+    want_ct, want_tags = oracle.ragged_encrypt(w.key, w.base_iv, off, ln, w.payload, w.extra["aad"], 3,
+                                               out=np.full(w.payload.size, FILL, np.uint8))
+    d_pt, d_aad = dev(w.payload), dev(w.extra["aad"])
+    s = torch.cuda.Stream()
+    for warm in (0, 1, 6):
+        outs = []
+        with torch.cuda.stream(s):
+            for _ in range(warm):
+                F.encrypt_tag_ragged(w.key, w.base_iv, off, ln, d_pt, d_aad, out=dev(np.zeros(w.payload.size, np.uint8)))
+        torch.cuda.synchronize()
+        say("capture after", warm, "calls")
+        mark, out = torch.zeros(16, device="cuda"), torch.zeros_like(d_pt)
+        tags = torch.zeros((off.size, 16), dtype=torch.uint8, device="cuda")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            with pytest.raises(F.FastrackError, match="captured"):
+                F.encrypt_tag_ragged(w.key, w.base_iv, off, ln, d_pt, d_aad, out=out, tags=tags)
+            mark.fill_(2.0)
+        g.replay()
+        assert host(mark).tolist() == [2.0] * 16 and not host(out).any() and not host(tags).any()
+        with torch.cuda.stream(s):
+            for _ in range(5):
+                outs.append(F.encrypt_tag_ragged(w.key, w.base_iv, off, ln, d_pt, d_aad,
+                                                 out=dev(np.full(w.payload.size, FILL, np.uint8))))
+        for ct, tg in outs:
+            assert np.array_equal(host(ct), want_ct) and np.array_equal(host(tg), want_tags)
