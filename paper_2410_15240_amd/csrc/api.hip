@@ -1617,12 +1617,14 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     // the kernels of the call before: it waits only for the kernels that last read this
     // slot (kRaggedRing calls back), and the kernels of this call wait for it. Small
     // tables go up on the caller's stream: their upload takes 2 us, less than the two
-    // streams' waits for each other.
+    // streams' waits for each other. It waits for the slot's kernels too: a handle can stand
+    // for one stream per thread (hipStreamPerThread). On the stream that ran them the wait
+    // adds nothing to the stream's own order.
     hipError_t he;
     const void *host_dev = se->host_dev[slot];   // the staging buffer's device address
     const bool own = tab_bytes > kSmallTables;
     hipStream_t us = own ? se->up : s;
-    if (own && se->slot_used[slot] && (he = hipStreamWaitEvent(us, se->slot_free[slot], 0)) != hipSuccess)
+    if (se->slot_used[slot] && (he = hipStreamWaitEvent(us, se->slot_free[slot], 0)) != hipSuccess)
         return hip_fail(he, "hipStreamWaitEvent");
     if ((he = launch_upload(host_dev, tab, tab_bytes, us)) != hipSuccess)
         return hip_fail(he, "chain table upload");

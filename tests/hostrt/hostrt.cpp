@@ -366,6 +366,18 @@ void capture_ragged()
     EXPECT(g_races == 0);
 }
 
+// Two threads call on hipStreamPerThread, one handle for two streams: a table slot is not
+// rewritten while the other thread's kernels may read it. (Whole chains: no partials.)
+void per_thread()
+{
+    const std::vector<uint64_t> lens(300, 1000);   // 10 KiB of tables
+    for (int i = 0; i < 24; ++i) {
+        g_thread = (i * 7 / 3) & 1;
+        EXPECT(ragged(lens, kPerThread) == 0 && !g_last.split && g_last_tables_ok);
+    }
+    g_thread = 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -373,6 +385,8 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "capture_ragged")
         capture_ragged();
+    else if (what == "per_thread")
+        per_thread();
     else
         return 2;
     fastrack_shutdown();
