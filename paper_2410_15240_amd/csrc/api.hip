@@ -78,8 +78,9 @@ constexpr int kRaggedRing = 4;
 struct ScratchEntry {
     int dev;
     hipStream_t stream;
-    void *ptr;
-    size_t bytes;
+    void *base = nullptr;    // partials and masks of cut launches (scratch_for)
+    void *large = nullptr;   // and of ragged ones that need more
+    size_t large_bytes = 0;
     // pinned host staging buffers for the tables of ragged launches, used in turn,
     // and for each the event after the upload that last read it
     void *host[kRaggedRing] = {};
@@ -231,51 +232,56 @@ int key_ctx(const uint8_t *key, hipStream_t s, int dev, const KeyCtx **out)
     return FASTRACK_OK;
 }
 
-// Scratch of at least `bytes` private to (device, stream): work on one stream
-// is ordered. Zeroed when (re)allocated; every launch rewrites what it reads.
+// The partials and masks of cut launches: private to (device, stream), as work on one stream
+// is ordered. The base area holds those of every cut uniform launch and is made with the
+// stream's first cut launch of either kind, so that a stream that ran one can be captured with
+// uniform calls, and it is kept until the library shuts down: graphs hold its address. Ragged
+// launches that need more (uniform ones never do) take a second area, which grows. Neither is
+// cleared: every launch writes what it reads.
+constexpr uint64_t kMaxPartials = FASTRACK_NOALLOC_MAX_PARTIALS;
+constexpr size_t kScratchBytes = (size_t)kMaxPartials * 16;
+
 int scratch_for(int dev, hipStream_t s, size_t bytes, void **out)
 {
     ScratchEntry *e = nullptr;
     for (auto &x : g_scratch)
         if (x.dev == dev && x.stream == s)
             e = &x;
-    if (e && e->bytes >= bytes) {
-        *out = e->ptr;
+    if (!e) {
+        g_scratch.push_back(ScratchEntry{dev, s});
+        e = &g_scratch.back();
+    }
+    hipError_t he;
+    if (!e->base && (he = hipMalloc(&e->base, kScratchBytes)) != hipSuccess) {
+        e->base = nullptr;
+        return fail(FASTRACK_ENOMEM, "hipMalloc(%zu) for scratch: %s", kScratchBytes, hipGetErrorString(he));
+    }
+    if (bytes <= kScratchBytes) {
+        *out = e->base;
         return FASTRACK_OK;
     }
-    if (!e) {
-        g_scratch.push_back(ScratchEntry{dev, s, nullptr, 0});
-        e = &g_scratch.back();
-    } else {
-        hipError_t he = hipStreamSynchronize(s);   // earlier launches may still use the old area
-        if (he != hipSuccess)
-            return hip_fail(he, "hipStreamSynchronize");
-        (void)hipFree(e->ptr);
-        e->ptr = nullptr;
-        e->bytes = 0;
+    if (e->large_bytes < bytes) {
+        if (e->large) {
+            if ((he = hipStreamSynchronize(s)) != hipSuccess)   // earlier launches may still use the old area
+                return hip_fail(he, "hipStreamSynchronize");
+            (void)hipFree(e->large);
+            e->large_bytes = 0;
+        }
+        if ((he = hipMalloc(&e->large, bytes)) != hipSuccess) {
+            e->large = nullptr;
+            return fail(FASTRACK_ENOMEM, "hipMalloc(%zu) for scratch: %s", bytes, hipGetErrorString(he));
+        }
+        e->large_bytes = bytes;
     }
-    hipError_t he = hipMalloc(&e->ptr, bytes);
-    if (he != hipSuccess) {
-        e->ptr = nullptr;
-        return fail(FASTRACK_ENOMEM, "hipMalloc(%zu) for scratch: %s", bytes, hipGetErrorString(he));
-    }
-    he = hipMemsetAsync(e->ptr, 0, bytes, s);
-    if (he != hipSuccess) {
-        (void)hipFree(e->ptr);
-        e->ptr = nullptr;
-        return hip_fail(he, "hipMemsetAsync of scratch");
-    }
-    e->bytes = bytes;
-    *out = e->ptr;
+    *out = e->large;
     return FASTRACK_OK;
 }
 
-// True if launches on a stream being captured must do without scratch of `bytes`: none can
-// be allocated there.
-bool capture_lacks_scratch(int dev, hipStream_t s, size_t bytes)
+// True if launches on a stream being captured must do without scratch: none can be allocated there.
+bool capture_lacks_scratch(int dev, hipStream_t s)
 {
     for (auto &x : g_scratch)
-        if (x.dev == dev && x.stream == s && x.bytes >= bytes)
+        if (x.dev == dev && x.stream == s && x.base)
             return false;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
@@ -291,7 +297,7 @@ int staging_for(int dev, hipStream_t s, size_t bytes, uint8_t **out)
         if (x.dev == dev && x.stream == s)
             e = &x;
     if (!e) {
-        g_scratch.push_back(ScratchEntry{dev, s, nullptr, 0});
+        g_scratch.push_back(ScratchEntry{dev, s});
         e = &g_scratch.back();
     }
     e->cur = (e->cur + 1) % kRaggedRing;
@@ -401,8 +407,6 @@ double plan_cost(const PlanCost &pc, uint64_t n, uint64_t qc, uint64_t q_last, u
 // wave-items that do not divide evenly over the waves leave a last pass in which
 // most of them idle. Chains are cut only if the items and chains together stay within
 // max_partials, the slots of their partials and masks (0: whole chains).
-constexpr uint64_t kMaxPartials = FASTRACK_NOALLOC_MAX_PARTIALS;
-
 void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_base, uint64_t slots, GcmLaunch &p,
                uint64_t max_partials = kMaxPartials)
 {
@@ -521,13 +525,11 @@ int run_gcm(bool encrypt, GcmMode mode, const KeyCtx *ctx, const uint8_t *base_i
     std::memset(&p, 0, sizeof p);
     const uint64_t slots = (uint64_t)num_cu * kGcmWavesPerWg * gcm_wgs_per_cu(mode);
     make_plan(mode, len, chain_bytes, chain_base, slots, p);
-    // The scratch of any cut launch is taken at the size that holds every one, so that a
-    // stream that ran one can be captured with others. Under capture and with none, chains
-    // of up to 4 KiB, and of any size if there is one for every wave, run whole.
-    constexpr size_t kScratchBytes = (size_t)kMaxPartials * 16;
+    // Under capture and without scratch, chains of up to 4 KiB, and of any size if there is
+    // one for every wave, run whole.
     const bool ghash = mode == kFused || mode == kVerify || mode == kApplyKs;
     if (ghash && p.n_items > p.n_chains && !fixed_scratch && (p.qc <= 256 || p.n_chains >= slots) &&
-        capture_lacks_scratch(dev, s, kScratchBytes))
+        capture_lacks_scratch(dev, s))
         make_plan(mode, len, chain_bytes, chain_base, slots, p, 0);
     if (p.n_items > 0xFFFFFFFFull)   // the kernel indexes a launch's items in 32 bits
         return fail(FASTRACK_EINVAL, "more than 2^32-1 work items in one launch");
@@ -567,8 +569,7 @@ int run_gcm(bool encrypt, GcmMode mode, const KeyCtx *ctx, const uint8_t *base_i
             p.partials = fixed_scratch;
         } else {
             void *sc = nullptr;
-            const size_t bytes = (size_t)(p.n_items + p.n_chains) * 16;
-            int rc = scratch_for(dev, s, bytes > kScratchBytes ? bytes : kScratchBytes, &sc);
+            int rc = scratch_for(dev, s, (size_t)(p.n_items + p.n_chains) * 16, &sc);
             if (rc)
                 return rc;
             p.partials = reinterpret_cast<uint4 *>(sc);
@@ -1750,7 +1751,8 @@ FT_EXPORT void fastrack_shutdown(void)
     }
     g_pools.clear();
     for (auto &s : g_scratch) {
-        (void)hipFree(s.ptr);
+        (void)hipFree(s.base);
+        (void)hipFree(s.large);
         (void)hipFree(s.rtab);
         for (int b = 0; b < kRaggedRing; ++b) {
             if (s.host[b])

@@ -378,6 +378,45 @@ void per_thread()
     g_thread = 0;
 }
 
+// Uniform calls captured on a stream that ragged calls have used, small and large ones: they
+// find scratch there, and no later call frees what the graph's kernels write.
+void scratch_area()
+{
+    const std::vector<uint64_t> cut(16, 1 << 20), whole(300, 1000);
+    std::vector<uint64_t> many(250000, 16);   // more partials and masks than any uniform launch has
+    many.push_back(64 << 20);
+    uintptr_t h = 0x200;
+    for (const auto &first : {cut, many}) {
+        const uintptr_t s = ++h;
+        EXPECT(ragged(first, s) == 0 && g_last.split && g_last_tables_ok);
+        (void)hipDeviceSynchronize();   // as before any capture
+        Stream &st = stream_at(S(s));
+        st.capturing = true;
+        const int refused = g_refused;
+        EXPECT(uniform(1 << 20, 64 << 10, s) == 0 && g_last.split);
+        EXPECT(g_refused == refused);
+        st.capturing = false;
+        const uint8_t *area = reinterpret_cast<const uint8_t *>(g_last.partials);
+        for (const auto &next : {many, cut, whole, many})
+            EXPECT(ragged(next, s) == 0 && g_last_tables_ok);
+        bool alive = false;
+        for (auto &m : g_mem)
+            alive |= (uintptr_t)area >= m.first && (uintptr_t)area + 16 <= m.first + m.second;
+        EXPECT(alive);
+        EXPECT(uniform(1 << 20, 64 << 10, s) == 0);
+        EXPECT(reinterpret_cast<const uint8_t *>(g_last.partials) == area);
+    }
+    // A capturing stream with none: one chain for every wave, and chains of up to 4 KiB, run whole.
+    for (auto lc : {std::pair<uint64_t, uint64_t>{4111ull * 289 * 16, 289 * 16}, {1 << 20, 4096}, {300 << 10, 2048}}) {
+        Stream &st = stream_at(S(++h));
+        st.capturing = true;
+        const int refused = g_refused;
+        EXPECT(uniform(lc.first, lc.second, h) == 0 && !g_last.split);
+        EXPECT(g_refused == refused);
+        st.capturing = false;
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -387,6 +426,8 @@ int main(int argc, char **argv)
         capture_ragged();
     else if (what == "per_thread")
         per_thread();
+    else if (what == "scratch_area")
+        scratch_area();
     else
         return 2;
     fastrack_shutdown();

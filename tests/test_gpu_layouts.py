@@ -111,3 +111,48 @@ def test_captured_on_a_stream_without_scratch(F):
         assert np.array_equal(host(flags), want_ok)
         assert np.array_equal(host(out), w.payload)
         F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags)
+
+
+def test_captured_on_a_stream_of_ragged_calls(F):
+    """A call whose chains are cut, captured on a stream that only ragged calls have used: it is
+    accepted, and every replay gives the eager results, also after a ragged call that needs
+    more scratch than any uniform one has come between."""
+    import torch
+    length, chain = 1 << 20, 64 << 10
+    w = W.random_case(6, length, chain)
+    ct, tags = oracle.chains_encrypt(w.key, w.base_iv, chain, w.payload, None, 0)
+    W.flip_bit(tags.reshape(-1)[3 * 16:], 5)
+    want_ok = np.ones(16, np.uint8)
+    want_ok[3] = 0
+    d_ct, d_tags = dev(ct), dev(tags)
+    out, flags = torch.zeros_like(d_ct), torch.zeros(16, dtype=torch.uint8, device="cuda")
+    cut = W.ragged_case(4003, [70000, 5, 200000, 0, 33], None, 0)
+    many = W.ragged_case(4004, [16] * 240000 + [3 << 20], None, 0)   # over 480,000 partials and masks
+    s = torch.cuda.Stream()
+    bufs = {}
+
+    def ragged(r):
+        off, ln = r.extra["chain_off"], r.extra["chain_len"]
+        if id(r) not in bufs:
+            bufs[id(r)] = (oracle.ragged_encrypt(r.key, r.base_iv, off, ln, r.payload, None, 0), dev(r.payload))
+        (want_c, want_t), pt = bufs[id(r)]
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            c, t = F.encrypt_tag_ragged(r.key, r.base_iv, off, ln, pt, out=torch.zeros_like(pt))
+        assert np.array_equal(host(t), want_t) and np.array_equal(host(c), want_c)
+
+    ragged(cut)
+    F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags)   # (the key's tables, on another stream)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        F.decrypt_verify(w.key, w.base_iv, chain, d_ct, d_tags, out=out, ok=flags)
+    for between in (None, many, cut, None):
+        if between is not None:
+            ragged(between)
+        out.zero_()
+        flags.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        assert np.array_equal(host(flags), want_ok)
+        assert np.array_equal(host(out), w.payload)
