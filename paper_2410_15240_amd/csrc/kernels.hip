@@ -1355,8 +1355,7 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
 
 // Chains cut into segments: T = mask xor the XOR of the chain's weighted
 // partials. 2^GL lanes per chain: they load the partials side by side and
-// XOR-sum them. 64 lanes where chains have many segments, 8 where they have few on the
-// average (16,384 chains of 3 segments on the average: 6.8 -> 4.3 us).
+// XOR-sum them (chain_tag_lanes_log2 chooses 8 or 64).
 constexpr int kTagThreads = 256;
 
 template <bool ENC, bool RAG, int GL>
@@ -1494,7 +1493,7 @@ static hipError_t launch_mode(const GcmLaunch &p, int num_cu, hipStream_t s)
     if (e != hipSuccess || !ghash || !p.split || q.wg_tag)
         return e;
     auto blocks = [&](uint32_t per_block) { return dim3((p.n_chains - 1) / per_block + 1); };
-    if (p.n_chains >= 1024 && p.n_items <= 16ull * p.n_chains)
+    if (chain_tag_lanes_log2(p) == 3)
         hipLaunchKernelGGL((chain_tag_kernel<ENC, RAG, 3>), blocks(kTagThreads / 8), dim3(kTagThreads), 0, s, p);
     else
         hipLaunchKernelGGL((chain_tag_kernel<ENC, RAG, 6>), blocks(kTagThreads / 64), dim3(kTagThreads), 0, s, p);

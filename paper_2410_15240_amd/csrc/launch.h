@@ -77,7 +77,7 @@ struct GcmLaunch {
     uint64_t chain_base;        // global index of chain 0 (IV, tag, AAD and ok indexing)
     uint64_t n_items;
     uint32_t n_chains;
-    uint32_t qc;                // blocks in a full chain
+    uint32_t qc;                // blocks in a full chain (ragged: in the longest)
     uint32_t q_last;            // blocks in the last chain (a partial block counts as one)
     uint32_t seg_log2;
     uint32_t lanes_log2;        // lanes per item: 4 (16), 5 (32) or 6 (64); the Horner stride
@@ -109,11 +109,23 @@ struct GcmLaunch {
     // chain's mask (one lane per chain) and the working waves skip theirs.
     uint32_t idle_masks;
     // Ragged launches (chains of their own lengths and offsets): the chain table
-    // and each item's chain; chain_bytes, qc, last_len and the segs_* fields
-    // are then unused. NULL for uniform chains.
+    // and each item's chain; chain_bytes, last_len and the segs_* fields are
+    // then unused. NULL for uniform chains.
     const RaggedChain *rchains;
     const uint32_t *ritem_chain;
 };
+
+// Lanes per chain (their log2) of the kernel that sums a cut launch's partials into tags: 8
+// where many chains have few segments, so that a wave serves eight of them, 64 otherwise. A
+// chain's lanes take its segments in turn, so the longest chain must be short too. 16,384
+// chains of 3 segments 4.5 us with 8 lanes, 6.1 with 64; with one of 64 segments among them
+// 4.3 and 5.8, of 128 5.0 and 5.6, of 256 8.1 and 5.5, of 1024 34.7 and 8.7. 1,024 chains with
+// one of 64: 3.9 and 3.9, of 128 4.6 and 4.0.
+inline int chain_tag_lanes_log2(const GcmLaunch &p)
+{
+    const uint64_t longest = ((uint64_t)p.qc + ((1ull << p.seg_log2) - 1)) >> p.seg_log2;
+    return p.n_chains >= 1024 && p.n_items <= 16ull * p.n_chains && longest <= 64 ? 3 : 6;
+}
 
 hipError_t launch_key_setup(const uint32_t key_words[8], KeyCtx *ctx, hipStream_t s);
 hipError_t launch_gcm(const GcmLaunch &p, bool encrypt, GcmMode mode, int num_cu, hipStream_t s);

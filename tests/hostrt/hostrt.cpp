@@ -417,6 +417,34 @@ void scratch_area()
     }
 }
 
+// The lanes of a chain's tag follow the longest chain as well as the average one.
+void tag_lanes()
+{
+    std::vector<uint64_t> lens(4097, 1024);
+    for (uint64_t big : {1ull << 24, 1ull << 28, 1ull << 30}) {
+        lens[2048] = big;
+        EXPECT(ragged(lens, 0x300) == 0 && g_last.split && g_last_tables_ok);
+        EXPECT((big / 16 >> g_last.seg_log2) <= 64 || chain_tag_lanes_log2(g_last) == 6);
+    }
+    std::vector<uint64_t> few(16384);   // a few segments each
+    for (size_t i = 0; i < few.size(); ++i)
+        few[i] = i * 7919 % 24000;
+    EXPECT(ragged(few, 0x300) == 0 && g_last.split && chain_tag_lanes_log2(g_last) == 3);
+    GcmLaunch p;
+    std::memset(&p, 0, sizeof p);
+    p.seg_log2 = 8;
+    for (uint32_t segs = 1; segs <= 130; ++segs)
+        for (uint32_t short_by : {0u, 1u, 255u}) {
+            p.qc = segs * 256 - short_by;
+            for (uint64_t n : {1023, 1024, 100000})
+                for (uint64_t mean : {2, 16, 17}) {
+                    p.n_chains = (uint32_t)n;
+                    p.n_items = n * mean;
+                    EXPECT(chain_tag_lanes_log2(p) == (n >= 1024 && mean <= 16 && segs <= 64 ? 3 : 6));
+                }
+        }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -428,6 +456,8 @@ int main(int argc, char **argv)
         per_thread();
     else if (what == "scratch_area")
         scratch_area();
+    else if (what == "tag_lanes")
+        tag_lanes();
     else
         return 2;
     fastrack_shutdown();

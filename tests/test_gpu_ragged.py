@@ -108,6 +108,9 @@ CASES = [
     ("wave-pads-short", [16, 64 * KiB, 16, 48, 64 * KiB + 1, 0, 256, 4096] * 8, None, 0),
     # short chains only (at most 64 blocks): whole chains, tagged in the streaming kernel
     ("whole-chains", lens_of(9, 20000, 200, 1024), None, 1),
+    # tags summed by 8 lanes a chain (many chains of few segments), and by 64 next to a long chain
+    ("tag-lanes8", lens_of(11, 1030, 1, 30000), None, 1),
+    ("tag-lanes64-one-long", lens_of(12, 1030, 1, 2000) + [5 * MiB + 3], None, 0),
 ]
 
 
