@@ -1409,6 +1409,122 @@ int ragged_slot(int dev, hipStream_t s, int b, size_t bytes, ScratchEntry **out_
     return FASTRACK_OK;
 }
 
+// Items of a chain of x blocks with segments of 2^g: max(1, ceil(x / 2^g)) (no overflow for x < 2^32).
+uint32_t segs_of(uint32_t x, uint32_t g)
+{
+    const uint32_t sg = (x >> g) + ((x & ((1u << g) - 1)) != 0);
+    return sg ? sg : 1u;
+}
+
+// A sample of a ragged launch's chains for the plan's estimate: chain k stands for w[k] chains
+// of y[k] + 1 blocks. All chains of a launch of up to kPlanSample; of a larger one as many
+// points over the chains' lengths laid end to end, each chain kPlanChainCost blocks longer than
+// it is, for its set-up and tail: long chains are met in proportion to their blocks, short
+// ones to their number. The points' distances vary (multiples of the golden section), so
+// that they keep no step with a layout that repeats. upto[j]: the blocks before chain 16 j.
+constexpr uint32_t kPlanSample = 128;
+constexpr uint64_t kPlanChainCost = 64;
+
+struct RaggedSample {
+    uint32_t m = 0;
+    uint32_t y[kPlanSample];
+    double w[kPlanSample];
+    void add(uint32_t x, double weight)
+    {
+        if (x) {   // an empty chain has no iterations
+            y[m] = x - 1;
+            w[m++] = weight;
+        }
+    }
+};
+
+void sample_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint64_t blocks, RaggedSample &r)
+{
+    if (n <= kPlanSample) {
+        for (uint64_t i = 0; i < n; ++i)
+            r.add(q[i], 1.0);
+        return;
+    }
+    const double step = ((double)blocks + (double)(n * kPlanChainCost)) / kPlanSample;
+    const uint64_t groups = (n + 15) / 16;
+    uint64_t j = 0;
+    double u = 0.3;
+    for (uint32_t k = 0; k < kPlanSample; ++k) {
+        u += 0.61803398874989;
+        u -= u >= 1.0 ? 1.0 : 0.0;
+        const double at = ((double)k + u) * step;
+        while (j + 1 < groups && (double)(upto[j + 1] + 16 * (j + 1) * kPlanChainCost) <= at)
+            ++j;
+        uint64_t i = 16 * j, end = upto[j] + i * kPlanChainCost + q[i] + kPlanChainCost;
+        while (i + 1 < n && (double)end <= at)
+            end += q[++i] + kPlanChainCost;
+        r.add(q[i], step / (double)(q[i] + kPlanChainCost));
+    }
+}
+
+// Lanes per item and one segment size for all chains of a ragged launch (2^lg blocks, at least
+// 4 iterations of the item's lanes), the pair with the least estimated time. Chains of
+// their own lengths load the waves unevenly when each takes few items; cut finer, they
+// pay a set-up and a tail more often. The estimate has the units of plan_cost: the items'
+// iterations and about one per item for set-up and tail over the waves, and a last, partial
+// pass of the shortest segments 0 (the items' order ends with them). (1024 samples of
+// 16 chains: 16 lanes and 256 blocks, 186 us; 128 blocks 193, 512 188. 256 samples: 32 lanes
+// and 512 blocks, 63 us; 256 blocks 66, 64 lanes and 256 blocks 72; with a tag kernel of
+// 64 lanes per chain.) Over 36 measured layouts from 5 to 22,400 chains the pair taken is on
+// the average 1.03 times and at most 1.14 times the best of its candidates; every 32nd chain
+// as the sample instead took 143 -> 852 us where each 16th chain was the long one, and 279 ->
+// 431 for 4,096 chains of 1 KiB beside one of 256 MiB.
+struct RaggedPlan {
+    uint32_t lanes_log2, seg_log2;
+};
+
+RaggedPlan plan_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint64_t blocks, uint32_t qmax, uint64_t slots)
+{
+    const PlanCost pc = plan_cost_of(kFused);
+    RaggedSample r;
+    sample_ragged(q, n, upto, blocks, r);
+    uint32_t lg0 = ceil_log2(qmax > 0 ? qmax : 1);
+    if (lg0 > 31)
+        lg0 = 31;
+    auto cost = [&](uint32_t l, uint32_t g) {
+        const uint32_t step = (1u << l) - 1, mask = (1u << g) - 1;
+        double full = 0, rest_it = 0;   // full segments; iterations of the segments 0
+        for (uint32_t k = 0; k < r.m; ++k) {
+            full += r.w[k] * (double)(r.y[k] >> g);
+            rest_it += r.w[k] * (double)(((r.y[k] & mask) >> l) + 1);
+        }
+        const double scale = 1.0 / (double)(64u >> l) / (double)slots;   // wave-items per wave
+        const uint32_t longest = (uint32_t)((((uint64_t)(qmax < mask ? qmax : mask) + 1) + step) >> l);
+        const double p0 = (double)n * scale, passes = full * scale + p0;
+        const double it = (full * (double)((mask >> l) + 1) + rest_it) * scale;   // iterations per wave
+        const double least = (double)longest * pc.floor + pc.item;
+        const double done = (double)(uint64_t)passes, part = passes - done;
+        const double w = 1.0 - pc.slope * (1.0 - part), share = w > pc.floor ? w : pc.floor;
+        double t;
+        if (passes < 1.0) {
+            t = it / passes * share + pc.item;
+        } else {
+            const double last = p0 >= part ? 0.7 * rest_it / (double)n : (double)((mask >> l) + 1);
+            t = it - part * last + done * pc.item + (part > 0 ? last * share + pc.item : 0.0);
+        }
+        return t > least ? t : least;
+    };
+    uint32_t ll = 6, lg = lg0;
+    double best = -1;
+    for (uint32_t l = 6; l >= 4; --l)
+        for (uint32_t g = lg0 < 5 ? 5 : lg0;; --g) {   // (1u << g of short chains: whole chains)
+            const double c = cost(l, g);
+            if (best < 0 || c < best) {
+                best = c;
+                ll = l;
+                lg = g;
+            }
+            if (g <= l + 2 || blocks >> g >= (8 * slots) << (6 - l))
+                break;
+        }
+    return {ll, lg < lg0 ? lg : lg0};
+}
+
 int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const uint64_t *h_off, const uint64_t *h_len,
                uint64_t n, const uint8_t *in, uint8_t *out, const uint8_t *aad, uint32_t aad_bytes,
                const uint8_t *tags_in, uint8_t *tags_out, uint8_t *ok, void *stream)
@@ -1425,8 +1541,12 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     uint64_t end = 0, blocks = 0, qmax = 0;
     // per-call work arrays, kept per thread so that calls do not allocate them
     thread_local std::vector<uint32_t> q, it0, order, cnt;
+    thread_local std::vector<uint64_t> upto;   // blocks before every 16th chain
     q.resize(n);   // blocks of each chain (a partial block counts as one)
+    upto.resize((n + 15) / 16);
     for (uint64_t i = 0; i < n; ++i) {
+        if (i % 16 == 0)
+            upto[i / 16] = blocks;
         if (h_off[i] & 15)
             return fail(FASTRACK_EINVAL, "chain %llu starts at offset %llu, not a multiple of 16", (unsigned long long)i,
                         (unsigned long long)h_off[i]);
@@ -1468,65 +1588,9 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     if ((rc = key_ctx(key, s, dev, &ctx)))
         return rc;
 
-    // Plan: lanes per item and one segment size for all chains (2^lg blocks, at least 4
-    // iterations of the item's lanes), the pair with the least estimated time. Chains of
-    // their own lengths load the waves unevenly when each takes few items; cut finer, they
-    // pay a set-up and a tail more often. The estimate takes up to 512 of the chains and has
-    // the units of plan_cost: the items' iterations and about one per item for set-up and tail
-    // over the waves, and a last, partial pass of the shortest items. (1024 samples of 16
-    // chains: 16 lanes and 256 blocks, 186 us; 128 blocks 193, 512 188. 256 samples: 32 lanes
-    // and 512 blocks, 63 us; 256 blocks 66, 64 lanes and 256 blocks 72; with a tag kernel of
-    // 64 lanes per chain.)
     const uint64_t slots = (uint64_t)ncu * kGcmWavesPerWg;
-    uint32_t lg0 = ceil_log2(qmax > 0 ? qmax : 1);
-    if (lg0 > 31)
-        lg0 = 31;
-    // Items of a chain of x blocks with segments of 2^g: max(1, ceil(x / 2^g)) (no overflow for x < 2^32).
-    auto segs_of = [](uint32_t x, uint32_t g) {
-        const uint32_t sg = (x >> g) + ((x & ((1u << g) - 1)) != 0);
-        return sg ? sg : 1u;
-    };
-    const PlanCost pc = plan_cost_of(kFused);
-    const uint64_t stride = (n + 511) / 512;
-    auto ragged_cost = [&](uint32_t l, uint32_t g) {
-        const uint32_t step = (1u << l) - 1, mask = (1u << g) - 1;
-        uint64_t full = 0, rest_it = 0, taken = 0;   // full segments; iterations of the segments 0
-        for (uint64_t i = 0; i < n; i += stride, ++taken) {
-            const uint32_t x = q[i];
-            full += segs_of(x, g) - 1;
-            rest_it += ((uint64_t)(x ? ((x - 1) & mask) + 1 : 0u) + step) >> l;
-        }
-        const double scale = (double)n / (double)taken / (double)(64u >> l) / (double)slots;   // wave-items per wave
-        const uint32_t longest = (uint32_t)((((uint64_t)(qmax < mask ? qmax : mask) + 1) + step) >> l);
-        const double p0 = (double)taken * scale, passes = (double)full * scale + p0;
-        const double it = ((double)full * (double)((mask >> l) + 1) + (double)rest_it) * scale;   // iterations per wave
-        const double least = (double)longest * pc.floor + pc.item;
-        const double done = (double)(uint64_t)passes, part = passes - done;
-        const double w = 1.0 - pc.slope * (1.0 - part), share = w > pc.floor ? w : pc.floor;
-        double t;
-        if (passes < 1.0) {
-            t = it / passes * share + pc.item;
-        } else {
-            const double last = p0 >= part ? 0.7 * (double)rest_it / (double)taken : (double)((mask >> l) + 1);
-            t = it - part * last + done * pc.item + (part > 0 ? last * share + pc.item : 0.0);
-        }
-        return t > least ? t : least;
-    };
-    uint32_t ll = 6, lg = lg0;
-    double best = -1;
-    for (uint32_t l = 6; l >= 4; --l)
-        for (uint32_t g = lg0 < 5 ? 5 : lg0;; --g) {   // (1u << g of short chains: whole chains)
-            const double c = ragged_cost(l, g);
-            if (best < 0 || c < best) {
-                best = c;
-                ll = l;
-                lg = g;
-            }
-            if (g <= l + 2 || blocks >> g >= (8 * slots) << (6 - l))
-                break;
-        }
-    if (lg > lg0)
-        lg = lg0;
+    const RaggedPlan plan = plan_ragged(q.data(), n, upto.data(), blocks, (uint32_t)qmax, slots);
+    const uint32_t ll = plan.lanes_log2, lg = plan.seg_log2;
     auto items_at = [&](uint32_t g) {
         uint64_t t = 0;
         for (uint64_t i = 0; i < n; ++i)

@@ -29,7 +29,7 @@ def run(exe, *args, stdin=None):
     return r.returncode, r.stdout
 
 
-@pytest.mark.parametrize("what", ["capture_ragged", "per_thread", "scratch_area", "tag_lanes"])
+@pytest.mark.parametrize("what", ["capture_ragged", "per_thread", "scratch_area", "tag_lanes", "ragged_plan"])
 def test_host_state(exe, what):
     rc, out = run(exe, what)
     assert rc == 0 and ": 0 failures, 0 races" in out, out[-4000:]
