@@ -1467,10 +1467,9 @@ void sample_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint64_t
 // their own lengths load the waves unevenly when each takes few items; cut finer, they
 // pay a set-up and a tail more often. The estimate has the units of plan_cost: the items'
 // iterations and about one per item for set-up and tail over the waves, and a last, partial
-// pass of the shortest segments 0 (the items' order ends with them). (1024 samples of
-// 16 chains: 16 lanes and 256 blocks, 186 us; 128 blocks 193, 512 188. 256 samples: 32 lanes
-// and 512 blocks, 63 us; 256 blocks 66, 64 lanes and 256 blocks 72; with a tag kernel of
-// 64 lanes per chain.) Over 36 measured layouts from 5 to 22,400 chains the pair taken is on
+// pass of segments 0 (the items' order ends with them), at their mean length. (They are the
+// shortest ones, but 0.7 of the mean chooses the same plans and 0.5 slower ones.) Over 37
+// measured layouts from 5 to 22,400 chains the pair taken is on
 // the average 1.03 times and at most 1.14 times the best of its candidates; every 32nd chain
 // as the sample instead took 143 -> 852 us where each 16th chain was the long one, and 279 ->
 // 431 for 4,096 chains of 1 KiB beside one of 256 MiB.
@@ -1504,7 +1503,7 @@ RaggedPlan plan_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint
         if (passes < 1.0) {
             t = it / passes * share + pc.item;
         } else {
-            const double last = p0 >= part ? 0.7 * rest_it / (double)n : (double)((mask >> l) + 1);
+            const double last = p0 >= part ? rest_it / (double)n : (double)((mask >> l) + 1);
             t = it - part * last + done * pc.item + (part > 0 ? last * share + pc.item : 0.0);
         }
         return t > least ? t : least;
