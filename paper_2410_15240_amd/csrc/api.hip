@@ -1360,9 +1360,8 @@ FT_EXPORT int fastrack_pipeline_d2h_mode(const uint8_t *key, const uint8_t *base
 namespace {
 
 // Ragged chains: chain i = bytes [off[i], off[i] + len[i]) of in/out, IV_i, tag i,
-// AAD i, ok[i]. The chains are planned on the host (lanes per item from the mean
-// chain length, segments of one size for all chains) and the chain and item
-// tables go to the device through the stream's pinned staging.
+// AAD i, ok[i]. The chains are planned on the host (plan_ragged) and the chain and
+// item tables go to the device through the stream's pinned staging.
 // The ragged table slot b of (dev, s) with room for `bytes`, the upload stream and
 // events created on first use. Growing the slots waits for both streams first.
 int ragged_slot(int dev, hipStream_t s, int b, size_t bytes, ScratchEntry **out_e, uint8_t **out)
@@ -1421,20 +1420,33 @@ uint32_t segs_of(uint32_t x, uint32_t g)
 // points over the chains' lengths laid end to end, each chain kPlanChainCost blocks longer than
 // it is, for its set-up and tail: long chains are met in proportion to their blocks, short
 // ones to their number. The points' distances vary (multiples of the golden section), so
-// that they keep no step with a layout that repeats. upto[j]: the blocks before chain 16 j.
-constexpr uint32_t kPlanSample = 128;
+// that they keep no step with a layout that repeats. (Over 792 layouts of compressed samples,
+// by the estimate over all chains, the plans from 256 points are 1.011 times the best one on
+// the average, from 128 1.016, from 512 1.007.) upto[j]: the blocks before chain 16 j.
+constexpr uint32_t kPlanSample = 256;
 constexpr uint64_t kPlanChainCost = 64;
 
+typedef uint32_t Uints4 __attribute__((vector_size(16)));
+typedef int32_t Ints4 __attribute__((vector_size(16)));
+typedef double Doubles4 __attribute__((vector_size(32)));
+
 struct RaggedSample {
-    uint32_t m = 0;
-    uint32_t y[kPlanSample];
-    double w[kPlanSample];
+    uint32_t m = 0;   // chains; once it is complete, vectors
+    Uints4 y[kPlanSample / 4];
+    Doubles4 w[kPlanSample / 4];
     void add(uint32_t x, double weight)
     {
         if (x) {   // an empty chain has no iterations
-            y[m] = x - 1;
-            w[m++] = weight;
+            y[m / 4][m % 4] = x - 1;
+            w[m / 4][m % 4] = weight;
+            ++m;
         }
+    }
+    void complete()
+    {
+        while (m % 4)
+            add(1, 0.0);
+        m /= 4;
     }
 };
 
@@ -1443,6 +1455,7 @@ void sample_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint64_t
     if (n <= kPlanSample) {
         for (uint64_t i = 0; i < n; ++i)
             r.add(q[i], 1.0);
+        r.complete();
         return;
     }
     const double step = ((double)blocks + (double)(n * kPlanChainCost)) / kPlanSample;
@@ -1452,14 +1465,15 @@ void sample_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint64_t
     for (uint32_t k = 0; k < kPlanSample; ++k) {
         u += 0.61803398874989;
         u -= u >= 1.0 ? 1.0 : 0.0;
-        const double at = ((double)k + u) * step;
-        while (j + 1 < groups && (double)(upto[j + 1] + 16 * (j + 1) * kPlanChainCost) <= at)
+        const uint64_t at = (uint64_t)(((double)k + u) * step);
+        while (j + 1 < groups && upto[j + 1] + 16 * (j + 1) * kPlanChainCost <= at)
             ++j;
         uint64_t i = 16 * j, end = upto[j] + i * kPlanChainCost + q[i] + kPlanChainCost;
-        while (i + 1 < n && (double)end <= at)
+        while (i + 1 < n && end <= at)
             end += q[++i] + kPlanChainCost;
         r.add(q[i], step / (double)(q[i] + kPlanChainCost));
     }
+    r.complete();
 }
 
 // Lanes per item and one segment size for all chains of a ragged launch (2^lg blocks, at least
@@ -1469,10 +1483,10 @@ void sample_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint64_t
 // iterations and about one per item for set-up and tail over the waves, and a last, partial
 // pass of segments 0 (the items' order ends with them), at their mean length. (They are the
 // shortest ones, but 0.7 of the mean chooses the same plans and 0.5 slower ones.) Over 37
-// measured layouts from 5 to 22,400 chains the pair taken is on
-// the average 1.03 times and at most 1.14 times the best of its candidates; every 32nd chain
-// as the sample instead took 143 -> 852 us where each 16th chain was the long one, and 279 ->
-// 431 for 4,096 chains of 1 KiB beside one of 256 MiB.
+// measured layouts from 5 to 22,400 chains the pair taken is on the average 1.02 times and at
+// most 1.14 times the best of its candidates. With every n/512-th chain as the sample, 16,384
+// chains of which each 16th was the long one took 852 us where the best plan takes 143, and
+// 4,096 of 1 KiB beside one of 256 MiB 431 (279).
 struct RaggedPlan {
     uint32_t lanes_log2, seg_log2;
 };
@@ -1485,18 +1499,25 @@ RaggedPlan plan_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint
     uint32_t lg0 = ceil_log2(qmax > 0 ? qmax : 1);
     if (lg0 > 31)
         lg0 = 31;
-    auto cost = [&](uint32_t l, uint32_t g) {
+    uint32_t ll = 6, lg = lg0;
+    double best = -1;
+    auto weigh = [&](uint32_t l, uint32_t g) {
         const uint32_t step = (1u << l) - 1, mask = (1u << g) - 1;
-        double full = 0, rest_it = 0;   // full segments; iterations of the segments 0
-        for (uint32_t k = 0; k < r.m; ++k) {
-            full += r.w[k] * (double)(r.y[k] >> g);
-            rest_it += r.w[k] * (double)(((r.y[k] & mask) >> l) + 1);
-        }
-        const double scale = 1.0 / (double)(64u >> l) / (double)slots;   // wave-items per wave
         const uint32_t longest = (uint32_t)((((uint64_t)(qmax < mask ? qmax : mask) + 1) + step) >> l);
+        const double least = (double)longest * pc.floor + pc.item;
+        if (best >= 0 && least >= best)
+            return;   // (the sums are most of a call's planning, 6 to 9 us in all for 512 chains and more)
+        Doubles4 fs = {}, rs = {};
+        for (uint32_t k = 0; k < r.m; ++k) {   // (31 bits: g >= 5 and l >= 4)
+            const Ints4 f = (Ints4)(r.y[k] >> g), i0 = (Ints4)((r.y[k] & mask) >> l) + 1;
+            fs += r.w[k] * __builtin_convertvector(f, Doubles4);
+            rs += r.w[k] * __builtin_convertvector(i0, Doubles4);
+        }
+        const double full = fs[0] + fs[1] + fs[2] + fs[3];      // full segments
+        const double rest_it = rs[0] + rs[1] + rs[2] + rs[3];   // iterations of the segments 0
+        const double scale = 1.0 / (double)(64u >> l) / (double)slots;   // wave-items per wave
         const double p0 = (double)n * scale, passes = full * scale + p0;
         const double it = (full * (double)((mask >> l) + 1) + rest_it) * scale;   // iterations per wave
-        const double least = (double)longest * pc.floor + pc.item;
         const double done = (double)(uint64_t)passes, part = passes - done;
         const double w = 1.0 - pc.slope * (1.0 - part), share = w > pc.floor ? w : pc.floor;
         double t;
@@ -1506,18 +1527,16 @@ RaggedPlan plan_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint
             const double last = p0 >= part ? rest_it / (double)n : (double)((mask >> l) + 1);
             t = it - part * last + done * pc.item + (part > 0 ? last * share + pc.item : 0.0);
         }
-        return t > least ? t : least;
+        t = t > least ? t : least;
+        if (best < 0 || t < best) {
+            best = t;
+            ll = l;
+            lg = g;
+        }
     };
-    uint32_t ll = 6, lg = lg0;
-    double best = -1;
     for (uint32_t l = 6; l >= 4; --l)
         for (uint32_t g = lg0 < 5 ? 5 : lg0;; --g) {   // (1u << g of short chains: whole chains)
-            const double c = cost(l, g);
-            if (best < 0 || c < best) {
-                best = c;
-                ll = l;
-                lg = g;
-            }
+            weigh(l, g);
             if (g <= l + 2 || blocks >> g >= (8 * slots) << (6 - l))
                 break;
         }
@@ -1578,15 +1597,15 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
         return fail(FASTRACK_EINVAL, "ragged calls cannot be captured: their chain tables are staged in buffers that "
                                      "later calls reuse");
 
-    std::lock_guard<std::mutex> lk(g_mu);
     int dev, ncu;
     int rc;
-    if ((rc = current_device(&dev, &ncu)))
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        rc = current_device(&dev, &ncu);
+    }
+    if (rc)
         return rc;
-    const KeyCtx *ctx;
-    if ((rc = key_ctx(key, s, dev, &ctx)))
-        return rc;
-
+    // (Before the lock is taken for the call: other threads' calls need not wait for the plan.)
     const uint64_t slots = (uint64_t)ncu * kGcmWavesPerWg;
     const RaggedPlan plan = plan_ragged(q.data(), n, upto.data(), blocks, (uint32_t)qmax, slots);
     const uint32_t ll = plan.lanes_log2, lg = plan.seg_log2;
@@ -1599,6 +1618,11 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     const uint64_t n_items = items_at(lg);
     if (n_items > 0xFFFFFFFFull)
         return fail(FASTRACK_EINVAL, "more than 2^32-1 work items");
+
+    std::lock_guard<std::mutex> lk(g_mu);
+    const KeyCtx *ctx;
+    if ((rc = key_ctx(key, s, dev, &ctx)))
+        return rc;
 
     // Device: chain table | item table | (split) partials | masks. Host: the two tables.
     // Tables (chain table | item table) go through pinned staging and an upload kernel
