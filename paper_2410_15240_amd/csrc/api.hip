@@ -1505,7 +1505,9 @@ RaggedPlan plan_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint
         const uint32_t step = (1u << l) - 1, mask = (1u << g) - 1;
         const uint32_t longest = (uint32_t)((((uint64_t)(qmax < mask ? qmax : mask) + 1) + step) >> l);
         const double least = (double)longest * pc.floor + pc.item;
-        if (best >= 0 && least >= best)
+        // A tag waits for 64 lanes to go over the longest chain's segments (0.2 us a step).
+        const double tag = 0.06 * (double)(((uint64_t)(qmax > 0 ? qmax - 1 : 0) >> g) / 64);
+        if (best >= 0 && least + tag >= best)
             return;   // (the sums are most of a call's planning, 6 to 9 us in all for 512 chains and more)
         Doubles4 fs = {}, rs = {};
         for (uint32_t k = 0; k < r.m; ++k) {   // (31 bits: g >= 5 and l >= 4)
@@ -1527,7 +1529,7 @@ RaggedPlan plan_ragged(const uint32_t *q, uint64_t n, const uint64_t *upto, uint
             const double last = p0 >= part ? rest_it / (double)n : (double)((mask >> l) + 1);
             t = it - part * last + done * pc.item + (part > 0 ? last * share + pc.item : 0.0);
         }
-        t = t > least ? t : least;
+        t = (t > least ? t : least) + tag;
         if (best < 0 || t < best) {
             best = t;
             ll = l;
