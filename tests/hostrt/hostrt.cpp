@@ -540,11 +540,54 @@ void ragged_plan()
     EXPECT(ragged(l, 0x400) == 0 && (1u << 20) >> g_last.seg_log2 <= 2048);
 }
 
+// Ragged calls on two streams without a wait between them: tables that go up on the caller's
+// stream and on the library's, alternating, whole and cut chains, table slots and scratch that
+// grow on the way. Nothing that a call queued is overwritten before it has run.
+void ring()
+{
+    uint64_t r = 99;
+    auto rnd = [&](uint64_t n) {
+        r = r * 6364136223846793005ull + 1442695040888963407ull;
+        return (r >> 33) % n;
+    };
+    int small = 0, large = 0, cut = 0;
+    for (int i = 0; i < 400; ++i) {
+        const uint64_t n = i < 20 ? 1 + rnd(100) : i == 60 ? 30000 : i == 120 ? 250001 : i == 121 ? 300001 : 1 + rnd(i % 3 ? 400 : 8000);
+        std::vector<uint64_t> lens(n);
+        for (auto &x : lens)
+            x = rnd(2000);
+        if (i % 5 == 0 || n > 200000)
+            lens[n / 2] = 4 << 20;
+        EXPECT(ragged(lens, 0x500 + (n > 200000 ? 0 : rnd(2))) == 0 && g_last_tables_ok);
+        const size_t tab = round256(g_last.n_chains * sizeof(RaggedChain)) + round256(g_last.n_items * 4);
+        (tab > kSmallTables ? large : small)++;
+        cut += g_last.split;
+    }
+    EXPECT(small > 100 && large > 80 && cut > 50);
+}
+
+// How a uniform call's chains are cut, in every mode: each line of the input names a mode, a
+// length, a chain size and a CU count, each line printed the plan's numbers (out of make_plan).
+int plans()
+{
+    int mode;
+    unsigned long long len, chain, cus;
+    while (scanf("%d %llu %llu %llu", &mode, &len, &chain, &cus) == 4) {
+        GcmLaunch p;
+        std::memset(&p, 0, sizeof p);
+        make_plan((GcmMode)mode, len, chain, 0, cus * kGcmWavesPerWg * gcm_wgs_per_cu(mode), p);
+        printf("%u %u %u %u %llu\n", p.lanes_log2, p.seg_log2, p.segs_full, p.segs_last, (unsigned long long)p.n_items);
+    }
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "plans")
+        return plans();
     if (what == "capture_ragged")
         capture_ragged();
     else if (what == "per_thread")
@@ -555,6 +598,8 @@ int main(int argc, char **argv)
         tag_lanes();
     else if (what == "ragged_plan")
         ragged_plan();
+    else if (what == "ring")
+        ring();
     else
         return 2;
     fastrack_shutdown();

@@ -6,7 +6,10 @@ Each layout pins one way the planner lays a launch out on a 256-CU GPU: 16, 32 o
 several with a last one that leaves waves idle (their numbering spreads it over
 the CUs). The results are compared bit for bit with the CPU oracle: plaintext and
 flags with one tampered chain, ciphertext and tags, and the two modes that check
-tags without AES."""
+tags without AES. The plan pinned beside a layout is that of decrypt + verify and
+encrypt + tag; the other modes weigh their costs differently (test_hostrt.py checks
+that the layouts together take every mode through 16, 32 and 64 lanes, whole chains
+and segments)."""
 import ctypes
 
 import numpy as np
@@ -30,6 +33,11 @@ LAYOUTS = [
     (14959, 7248, 5, (6, 1, 0)),
     (440001, 60016, 5, (6, 1, 0)),
     (2999999, 10000, 7, (6, 1, 0)),
+    (263735, 16, 0, (4, 0, 1)),
+    (12819, 48, 5, (6, 0, 0)),
+    (3794, 16, 0, (6, 0, 0)),
+    (27803887, 6784, 1, (4, 1, 1)),
+    (31764477, 1856, 13, (5, 0, 1)),
 ]
 
 

@@ -243,3 +243,39 @@ def test_capture_is_refused(F):
                                                  out=dev(np.full(w.payload.size, FILL, np.uint8))))
         for ct, tg in outs:
             assert np.array_equal(host(ct), want_ct) and np.array_equal(host(tg), want_tags)
+
+
+def test_calls_queued_without_a_wait(F):
+    """Fourteen calls on one stream with no synchronisation between them: tables below and above
+    64 KiB (uploaded on the caller's stream and on the library's) in turn, each slot used more
+    than once, the slots growing on the way. Every output against the oracle."""
+    import torch
+    layouts = [lens_of(20, 60, 0, 3000), lens_of(21, 2500, 0, 1500), lens_of(22, 30, 100000, 300000),
+               lens_of(23, 2300, 1, 900), [17], lens_of(24, 35000, 16, 200), lens_of(25, 12, 0, 50000),
+               lens_of(26, 3000, 0, 2000) + [2 * MiB], lens_of(27, 70, 0, 64), lens_of(28, 2400, 0, 64),
+               lens_of(29, 200, 0, 9000), lens_of(30, 2600, 300, 600), lens_of(31, 5, 0, 40), lens_of(32, 33, 0, 70000)]
+    key, iv = bytes(range(32)), bytes(range(12))   # one key: the set-up of a ninth would wait for the device
+    work = []
+    for k, lens in enumerate(layouts):
+        w = W.ragged_case(5000 + k, lens, None, 1)
+        off, ln, aad = w.extra["chain_off"], w.extra["chain_len"], w.extra["aad"]
+        ct, tags = oracle.ragged_encrypt(key, iv, off, ln, w.payload, aad, 1, out=w.payload.copy())
+        want_ok = np.ones(off.size, np.uint8)
+        want_ok[off.size // 2] = 0
+        tags[off.size // 2, 3] ^= 1
+        work.append((off, ln, w.payload, want_ok, dev(ct), dev(tags), dev(aad),
+                     torch.zeros(ct.size, dtype=torch.uint8, device="cuda"),
+                     torch.zeros(off.size, dtype=torch.uint8, device="cuda")))
+    say("queueing", len(work), "calls of", [len(x) for x in layouts], "chains")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        for off, ln, _, _, d_ct, d_tags, d_aad, out, ok in work:
+            F.decrypt_verify_ragged(key, iv, off, ln, d_ct, d_tags, d_aad, out=out, ok=ok)
+    torch.cuda.synchronize()
+    for k, (off, ln, payload, want_ok, _, _, _, out, ok) in enumerate(work):
+        assert np.array_equal(host(ok), want_ok), k
+        mask = np.zeros(payload.size, bool)
+        for o, l in zip(off.tolist(), ln.tolist()):
+            mask[o:o + l] = True
+        assert np.array_equal(host(out)[mask], payload[mask]) and not host(out)[~mask].any(), k
