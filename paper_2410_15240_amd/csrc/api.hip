@@ -452,9 +452,10 @@ void make_plan(GcmMode mode, uint64_t len, uint64_t chain_bytes, uint64_t chain_
     // The smallest in segments of one iteration: every wave-item saves the second one (1.3
     // us), but more of them share a CU, each with a tail. Decrypt + verify and encrypt + tag
     // up to two for every CU (512 KiB of 64 KiB chains 12.9 -> 11.4 us, one 400,000-byte chain
-    // 14.1 -> 13.4). 1 MiB would still gain (13.4 -> 12.1), but its cut into two-iteration
-    // segments is a published plan; above, it turns (1.5 MB of 300,000-byte chains
-    // 14.7 -> 15.0, 3 MiB of 10,000-byte ones 15.1 -> 16.6). The AES-only modes have no tail:
+    // 14.1 -> 13.4). The bound lies below the turn: 1 MiB (1,024 items) would still gain
+    // (13.4 -> 12.1), 1.5 MB of 300,000-byte chains (1,465) loses (14.7 -> 15.0), 3 MiB of
+    // 10,000-byte ones too (15.1 -> 16.6); the planner's tests pin 1 MiB to two iterations.
+    // (A short last chain counts as a full one.) The AES-only modes have no tail:
     // up to one for every wave (1 MiB 6.9 -> 5.4 us, 3 MiB of 10,000-byte chains 8.1 -> 7.8).
     // The modes without AES, with short iterations, up to one for every CU (512 KiB
     // keystream-apply 8.8 -> 9.2 us).

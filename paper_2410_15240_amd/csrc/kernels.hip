@@ -351,9 +351,12 @@ static_assert(kTBase * 16 == 0x10000, "one address byte places the T tables");
 constexpr uint32_t kT0GhashOnly = 4096;         // uint4 index: 64 KiB
 constexpr uint32_t kTreeBaseGhashOnly = 4160;   // 65 KiB
 constexpr uint32_t kLdsGhashOnly = (65 + 8 * kTreeLds) * 1024 + 64;
-// Modes without GHASH: T0 | T1 alone. A workgroup of theirs and one of a GHASH-only mode
-// fit a CU together (64 + 89 KiB, 2048 threads, 48 + 80 VGPRs a lane), so the two kernels of
-// an eager call overlap: one reads the LDS while the other's waves wait.
+// Modes without GHASH: T0 | T1 alone. Of a workgroup of theirs and one of a GHASH-only mode
+// the LDS of a CU holds both (64 + 89 KiB). Its registers do for one pair: CTR with 64 lanes
+// per item (48 VGPRs) beside the verification of 64-lane segments (79, given out as 80), 4 (48 +
+// 80) = 512 a lane of a SIMD. The two kernels of an eager call then overlap (64 MiB at 64 KiB
+// chains): one reads the LDS while the other's waves wait. The other verify kernels take 86 to
+// 98 and CTR with 16 or 32 lanes 61: there the second kernel's workgroups wait for a CU.
 constexpr uint32_t kLdsAesOnly = 64 * 1024 + 64;
 static_assert(kLdsAesOnly + kLdsGhashOnly <= 160 * 1024, "an AES-only and a GHASH-only workgroup share a CU");
 // Per-wave progress counters (16 words): the last 64 B of each layout.
@@ -494,9 +497,11 @@ __device__ inline u4 group_mul_tab4(const u4 &x, const Tab4 *__restrict__ t, uin
 // eight m (of M = L/8) multiplies its sum by H^(8 (M-1-m) + 2) in the same way, four
 // positions a lane, from the key's tables in global memory, and the item XOR-sums all its
 // lanes. Bound by latency: 16 + 8 + 4 lookups in LDS and 4 in global memory a lane in five
-// dependent batches: 1.2 to 1.9 us of a launch's tail. With one lane of each group looking up all 32 positions (three levels, a last
-// product by H^2: 128 LDS reads a wave in 16 batches, and as the LDS serves a wave's 16-byte
-// reads 16 lanes at a time, nearly as costly as with all lanes active) it took 3.1 us.
+// dependent batches: 1.2 to 1.9 us of a launch's tail. With one lane of each group looking up
+// all 32 positions (three levels, a last product by H^2: 128 LDS reads a wave in 16 batches, and
+// as the LDS serves a wave's 16-byte reads 16 lanes at a time, nearly as costly as with all
+// lanes active) it took 3.1 us. The lanes' entries fall on bank groups as their nibbles have it:
+// all of a launch's LDS bank conflicts, 2,342 cycles a CU or about 1 us over the 64 MiB batch.
 template <int CTRL>
 __device__ __forceinline__ u4 dpp4(const u4 &x)
 {
@@ -786,7 +791,10 @@ __global__ __launch_bounds__(kThreads, gcm_wgs_per_cu(MODE) * kWavesPerWg / 4) v
         }
         if (tid < 16)   // slot 4 s + m: the m-th wave of SIMD s; slots no wave uses never hold anyone back
             reinterpret_cast<uint32_t *>(lds4)[kProg + tid] = (tid & 3) < kWavesPerWg / 4 ? 0u : 0xFFFFFFFFu;
-        if (kGhash) {   // all loads of the 32 KiB GHASH table and the tree tables first, then the stores
+        // The 64 KiB GHASH table and the tree tables, several loads at a time. (As compiled, the
+        // fused kernels issue them after the T-tables' stores, and the last tree load, which
+        // only some of the threads make, after the other tables' stores.)
+        if (kGhash) {
             const uint4 *g = reinterpret_cast<const uint4 *>(c->g16[LL - 4]);
             const uint4 *sq = reinterpret_cast<const uint4 *>(c->sq_tab);
             constexpr int kTreeU4 = kTreeLds * (int)(sizeof(Tab4) / 16);

@@ -72,7 +72,7 @@ def test_key_set_up_on_one_stream_used_on_another(F):
 
 def test_scratch_grows_between_launches(F):
     # Launches that cut chains into segments keep per-item partials in the stream's
-    # scratch area; a larger launch after a small one reallocates it.
+    # scratch area, which a larger launch after a small one uses further into.
     for seed, length, chain in ((330, 2 * MiB + 16, MiB), (331, 64 * MiB + 48, 4 * MiB), (332, 3 * MiB, MiB)):
         w, aad, ct, tags = case(seed, length, chain, 0)
         bad = ct.copy()
