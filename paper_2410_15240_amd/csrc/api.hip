@@ -277,14 +277,22 @@ int scratch_for(int dev, hipStream_t s, size_t bytes, void **out)
     return FASTRACK_OK;
 }
 
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess)
+        return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();   // (the default stream, while another stream is captured: not an error of the next launch)
+    return false;
+}
+
 // True if launches on a stream being captured must do without scratch: none can be allocated there.
 bool capture_lacks_scratch(int dev, hipStream_t s)
 {
     for (auto &x : g_scratch)
         if (x.dev == dev && x.stream == s && x.base)
             return false;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+    return capturing(s);
 }
 
 // Pinned host staging of at least `bytes` for (device, stream), free to overwrite:
@@ -1595,8 +1603,7 @@ int run_ragged(bool encrypt, const uint8_t *key, const uint8_t *base_iv, const u
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // A replay would read the staging buffer and write the table slot that later calls on the
     // stream reuse, and would run this call's kernels on another call's tables.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+    if (capturing(s))
         return fail(FASTRACK_EINVAL, "ragged calls cannot be captured: their chain tables are staged in buffers that "
                                      "later calls reuse");
 

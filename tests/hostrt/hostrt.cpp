@@ -46,6 +46,7 @@ std::map<uintptr_t, size_t> g_mem;
 GcmLaunch g_last;      // the last launch, and how it was asked for
 int g_last_mode;
 bool g_last_tables_ok;
+hipError_t g_last_error = hipSuccess;   // as a launch's own check would find it
 
 const uintptr_t kPerThread = 2;   // hipStreamPerThread
 
@@ -165,7 +166,12 @@ bool tables_ok(const GcmLaunch &p)
 
 extern "C" {
 const char *hipGetErrorString(hipError_t) { return "error of the stand-in runtime"; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError()
+{
+    const hipError_t e = g_last_error;
+    g_last_error = hipSuccess;
+    return e;
+}
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
@@ -218,6 +224,8 @@ hipError_t hipStreamSynchronize(hipStream_t s)
 }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st)
 {
+    if (!s && any_capturing())
+        return g_last_error = hipErrorStreamCaptureImplicit;
     *st = stream_at(s).capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
@@ -287,7 +295,7 @@ hipError_t launch_upload(const void *src, void *dst, uint64_t n, hipStream_t s)
     touch(src, n, false, st.ctx, st.vc, "upload's read");
     touch(dst, n, true, st.ctx, st.vc, "upload");
     memcpy(dst, src, n);
-    return hipSuccess;
+    return hipGetLastError();
 }
 hipError_t launch_gcm(const GcmLaunch &p, bool, GcmMode mode, int, hipStream_t s)
 {
@@ -303,7 +311,7 @@ hipError_t launch_gcm(const GcmLaunch &p, bool, GcmMode mode, int, hipStream_t s
     }
     if (p.split)
         touch(p.partials, (p.n_items + p.n_chains) * 16, true, st.ctx, st.vc, "partials");
-    return hipSuccess;
+    return hipGetLastError();
 }
 hipError_t launch_seq_ghash(const GcmLaunch &, bool, hipStream_t s) { enqueue(s); return hipSuccess; }
 hipError_t launch_clock_probe(uint64_t, uint32_t, uint64_t *, hipStream_t) { return hipErrorUnknown; }
@@ -363,6 +371,15 @@ void capture_ragged()
             for (int i = 0; i < 6; ++i)
                 EXPECT(ragged(i & 1 ? small : lens, 0x100) == 0 && g_last_tables_ok);
         }
+    // The default stream while another is captured: the runtime refuses to say whether it is.
+    for (int i = 0; i < 5; ++i)
+        EXPECT(uniform(1 << 20, 64 << 10, 0x100) == 0 && ragged(small, 0) == 0);
+    (void)hipDeviceSynchronize();
+    EXPECT(ragged(small, 0x100) == 0);
+    stream_at(S(0x100)).capturing = true;
+    EXPECT(ragged(small, 0) == 0 && g_last_tables_ok);
+    EXPECT(uniform(1 << 20, 1024, 0) == 0);
+    stream_at(S(0x100)).capturing = false;
     EXPECT(g_races == 0);
 }
 
