@@ -270,6 +270,7 @@ def decrypt_verify(key, base_iv, chain_bytes, ct, tags, aad=None, out=None, ok=N
         _used_on(new, [stream], dev)
     return out, ok
 
+
 def decrypt_verify_noalloc(key, base_iv, chain_bytes, ct, tags, aad, out, ok, flags=0, stream=None):
     """decrypt_verify through the allocation-free entry point: the caller passes every
     buffer (out, ok) and the library allocates no device memory. Calls on one GPU
@@ -284,6 +285,7 @@ def decrypt_verify_noalloc(key, base_iv, chain_bytes, ct, tags, aad, out, ok, fl
           _host_bytes(base_iv, 12, "base_iv"), chain_bytes, ct.data_ptr(), size, tags_p, aad_p, aad_bytes, out_p, ok_p,
           flags, _raw_stream(stream, idx))
     return out, ok
+
 
 def encrypt_tag(key, base_iv, chain_bytes, pt, aad=None, out=None, tags=None, flags=0, stream=None):
     """Encrypt every chain of pt (uint8 CUDA tensor) and produce its tag. Returns (ct, tags)."""
@@ -517,7 +519,7 @@ def _ragged_layout(chain_off, chain_len, size, what):
 
 def decrypt_verify_ragged(key, base_iv, chain_off, chain_len, ct, tags, aad=None, out=None, ok=None, stream=None):
     """Decrypt + verify chains of their own offsets and lengths in ct (uint8 CUDA tensor). Returns (pt, ok);
-    bytes of pt outside every chain are left as they were."""
+    bytes of pt outside every chain are left as they were. Refused on a capturing stream."""
     _u8(ct, "ct")
     dev, idx, size = ct.device, ct.get_device(), ct.numel()
     off, ln = _ragged_layout(chain_off, chain_len, size, "ct")
@@ -541,7 +543,8 @@ def decrypt_verify_ragged(key, base_iv, chain_off, chain_len, ct, tags, aad=None
 
 
 def encrypt_tag_ragged(key, base_iv, chain_off, chain_len, pt, aad=None, out=None, tags=None, stream=None):
-    """Encrypt + tag chains of their own offsets and lengths in pt (uint8 CUDA tensor). Returns (ct, tags)."""
+    """Encrypt + tag chains of their own offsets and lengths in pt (uint8 CUDA tensor). Returns (ct, tags).
+    Refused on a capturing stream."""
     _u8(pt, "pt")
     dev, idx, size = pt.device, pt.get_device(), pt.numel()
     off, ln = _ragged_layout(chain_off, chain_len, size, "pt")
